@@ -235,12 +235,15 @@ enum ScalPhase {
   PH_RECHECK = 8,    // active = restart: the problems the last check restarted (no sum)
   PH_FORCE_RESTART = 9,  // test hook: every even-numbered problem with b != 0 restarts
 };
-void cg_scalar(int phase, CgScal* scal, int nprob, const int* poff, const int* pcnt,
-               const double* partial, double rtol, int max_iters, int* active_count,
+// max_slots: the longest slot list of any problem; active_count (nullable)
+// receives the number of active problems, added to what it holds; clear
+// (nullable) is set to 0
+void cg_scalar(int phase, CgScal* scal, int nprob, int max_slots, const int* poff, const int* pcnt,
+               const double* partial, double rtol, int max_iters, int* active_count, int* clear,
                hipStream_t s, int aux = 0);
 void scal_to_stats(const CgScal* scal, int nprob, double rtol, int* iters_max,
                    int* nonconv, double* relres_max, hipStream_t s);
-void sum_partials(int nprob, const int* poff, const int* pcnt, const double* partial,
+void sum_partials(int nprob, int slots, const int* poff, const int* pcnt, const double* partial,
                   double scale, double* dst, hipStream_t s);
 
 // ---- whole-field kernels on one grid (epilogue, control transfer) ----

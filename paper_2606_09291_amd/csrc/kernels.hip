@@ -76,21 +76,24 @@ __device__ __forceinline__ int xcd_swizzle(int b, int nb) {
   return (xcd < r ? xcd * (q + 1) : r * (q + 1) + (xcd - r) * q) + loc;
 }
 
-// Sum of a problem's c partial slots in slot order.  The loads are issued
-// sixteen at a time before their additions, so one thread's slots are in
-// flight together; the additions keep the sequential order, so the sum is
-// the same to the bit as a plain loop's.
-__device__ __forceinline__ double slot_sum(const double* __restrict__ v, int c) {
+// Sum of a problem's c partial slots by LP consecutive lanes (a power of two,
+// at most a wave): lane `sub` adds slots sub, sub + LP, ..., eight loads in
+// flight at a time, and the lanes' sums are added in a fixed butterfly, so the
+// sum is deterministic and every lane of the problem holds it.
+template <int LP>
+__device__ __forceinline__ double slots_sum(const double* __restrict__ v, int c, int sub) {
   double sum = 0.0;
-  int j = 0;
-  for (; j + 16 <= c; j += 16) {
-    double t[16];
+  int j = sub;
+  for (; j + 7 * LP < c; j += 8 * LP) {
+    double t[8];
 #pragma unroll
-    for (int u = 0; u < 16; ++u) t[u] = v[j + u];
+    for (int u = 0; u < 8; ++u) t[u] = v[j + u * LP];
 #pragma unroll
-    for (int u = 0; u < 16; ++u) sum += t[u];
+    for (int u = 0; u < 8; ++u) sum += t[u];
   }
-  for (; j < c; ++j) sum += v[j];
+  for (; j < c; j += LP) sum += v[j];
+#pragma unroll
+  for (int o = LP / 2; o > 0; o >>= 1) sum += __shfl_xor(sum, o, 64);
   return sum;
 }
 
@@ -2880,24 +2883,26 @@ void group_xflush(const GridArgs& g, double* x, const double* p0, const double* 
 // Per-problem scalar steps, one workgroup for all problems (fixed summation
 // order; integer count reduced in LDS).
 // ---------------------------------------------------------------------------
-// One thread per problem; the count of problems still active is gathered
-// with integer atomics (exact, order-independent) into a counter zeroed by
-// the caller's k_zero_int.
+// LP lanes per problem sum its partial slots and the first of them takes the
+// step.  The launch picks LP by the longest slot list: one thread alone walked
+// the 1024 slots of a 257^3 problem in 31 us, a wave takes 5; problems of one
+// slot (9^3) need no second lane.  The count of problems still active is
+// gathered with integer atomics (exact, order-independent) into a counter that
+// an earlier phase of the same iteration cleared (`clear`).
+template <int LP>
 __global__ void __launch_bounds__(256)
     k_cg_scalar(int phase, CgScal* scal, int nprob, const int* __restrict__ poff,
                 const int* __restrict__ pcnt, const double* __restrict__ partial, double rtol,
-                int max_iters, int* active_count, int aux) {
-  __shared__ int scount[256];
+                int max_iters, int* active_count, int aux, int* clear) {
+  __shared__ int scount[4];
   int cnt = 0;
   const double rt2 = rtol * rtol;
-  {
-    const int p = blockIdx.x * 256 + threadIdx.x;
-    if (p < nprob) {
+  const int sub = threadIdx.x % LP;
+  const int p = (blockIdx.x * 256 + threadIdx.x) / LP;
+  if (p < nprob) {
     double sum = 0.0;
-    if (partial) {
-      const int o = poff[p], c = pcnt[p];
-      sum = slot_sum(partial + o, c);
-    }
+    if (partial) sum = slots_sum<LP>(partial + poff[p], pcnt[p], sub);
+    if (sub == 0) {
     CgScal sc = scal[p];
     switch (phase) {
       case PH_INIT_BB:
@@ -2982,20 +2987,18 @@ __global__ void __launch_bounds__(256)
         break;
     }
     scal[p] = sc;
-    cnt += sc.active;
+    cnt = sc.active;
     }
   }
-  scount[threadIdx.x] = cnt;
+  if (clear && blockIdx.x == 0 && threadIdx.x == 0) *clear = 0;
+  if (!active_count) return;   // uniform
+  const unsigned long long on = __ballot(cnt != 0);
+  if ((threadIdx.x & 63) == 0) scount[threadIdx.x >> 6] = __popcll(on);
   __syncthreads();
-  for (int o = 128; o > 0; o >>= 1) {
-    if (threadIdx.x < o) scount[threadIdx.x] += scount[threadIdx.x + o];
-    __syncthreads();
+  if (threadIdx.x == 0) {
+    const int c = scount[0] + scount[1] + scount[2] + scount[3];
+    if (c) atomicAdd(active_count, c);
   }
-  if (threadIdx.x == 0 && active_count && scount[0]) atomicAdd(active_count, scount[0]);
-}
-
-__global__ void k_zero_int(int* x) {
-  if (threadIdx.x == 0) *x = 0;
 }
 
 __global__ void k_level_work_zero(EpiOut* out) {
@@ -3021,12 +3024,26 @@ void level_work_add(int count, int n, const int* prob_level, const CgScal* scal,
                      prob_level, scal, out);
 }
 
-void cg_scalar(int phase, CgScal* scal, int nprob, const int* poff, const int* pcnt,
-               const double* partial, double rtol, int max_iters, int* active_count,
+// lanes that sum one problem's slots: one up to 4 slots, 8 up to 64, else a wave
+static int slot_lanes(const double* partial, int max_slots) {
+  return !partial || max_slots <= 4 ? 1 : max_slots <= 64 ? 8 : 64;
+}
+
+void cg_scalar(int phase, CgScal* scal, int nprob, int max_slots, const int* poff, const int* pcnt,
+               const double* partial, double rtol, int max_iters, int* active_count, int* clear,
                hipStream_t s, int aux) {
-  if (active_count) hipLaunchKernelGGL(k_zero_int, dim3(1), dim3(64), 0, s, active_count);
-  hipLaunchKernelGGL(k_cg_scalar, dim3((nprob + 255) / 256), dim3(256), 0, s, phase, scal, nprob,
-                     poff, pcnt, partial, rtol, max_iters, active_count, aux);
+  const int lp = slot_lanes(partial, max_slots);
+#define MLSGD_LAUNCH(LP_)                                                                       \
+  hipLaunchKernelGGL(k_cg_scalar<LP_>, dim3(cdiv((long long)nprob * LP_, 256)), dim3(256), 0, s, \
+                     phase, scal, nprob, poff, pcnt, partial, rtol, max_iters, active_count, aux, \
+                     clear)
+  if (lp == 1)
+    MLSGD_LAUNCH(1);
+  else if (lp == 8)
+    MLSGD_LAUNCH(8);
+  else
+    MLSGD_LAUNCH(64);
+#undef MLSGD_LAUNCH
 }
 
 __global__ void __launch_bounds__(1024)
@@ -3067,17 +3084,28 @@ void scal_to_stats(const CgScal* scal, int nprob, double rtol, int* iters_max, i
                      nonconv, relres_max);
 }
 
+template <int LP>
 __global__ void k_sum_partials(int nprob, const int* poff, const int* pcnt,
                                const double* partial, double scale, double* dst) {
-  const int p = blockIdx.x * blockDim.x + threadIdx.x;
+  const int p = (blockIdx.x * blockDim.x + threadIdx.x) / LP;
   if (p >= nprob) return;
-  dst[p] = scale * slot_sum(partial + poff[p], pcnt[p]);
+  const double sum = slots_sum<LP>(partial + poff[p], pcnt[p], threadIdx.x % LP);
+  if (threadIdx.x % LP == 0) dst[p] = scale * sum;
 }
-void sum_partials(int nprob, const int* poff, const int* pcnt, const double* partial,
+void sum_partials(int nprob, int slots, const int* poff, const int* pcnt, const double* partial,
                   double scale, double* dst, hipStream_t s) {
   if (nprob <= 0) return;
-  hipLaunchKernelGGL(k_sum_partials, dim3(cdiv(nprob, 256)), dim3(256), 0, s, nprob, poff, pcnt,
-                     partial, scale, dst);
+  const int lp = slot_lanes(partial, slots);
+#define MLSGD_LAUNCH(LP_)                                                                          \
+  hipLaunchKernelGGL(k_sum_partials<LP_>, dim3(cdiv((long long)nprob * LP_, 256)), dim3(256), 0, s, \
+                     nprob, poff, pcnt, partial, scale, dst)
+  if (lp == 1)
+    MLSGD_LAUNCH(1);
+  else if (lp == 8)
+    MLSGD_LAUNCH(8);
+  else
+    MLSGD_LAUNCH(64);
+#undef MLSGD_LAUNCH
 }
 
 // ---------------------------------------------------------------------------

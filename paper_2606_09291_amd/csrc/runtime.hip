@@ -118,6 +118,7 @@ struct Plan {
   double* dwork = nullptr; // their factorisation's L^-1, same shape
   int dense_N = 0;
   long long npartial = 0;  // partial-sum slots (one per workgroup tile of every problem)
+  int max_slots = 0;       // longest slot list of a problem
   void* arena = nullptr;
   size_t arena_bytes = 0;
   uint64_t last_use = 0;   // plan-cache clock at the latest get_plan
@@ -372,6 +373,7 @@ void plan_layout(mlsgd_ctx* c, const std::vector<Block>& blocks, Plan* P) {
     P->h_pcnt[q] = make_tiling(P->h_n[q], c->tile_y, c->xchunk).tiles_per_row;
     P->h_poff[q] = (int)off;
     off += P->h_pcnt[q];
+    P->max_slots = std::max(P->max_slots, P->h_pcnt[q]);
   }
   require(off < (1LL << 31), "partial buffer too large");
   P->npartial = off;
@@ -1103,6 +1105,15 @@ void fmg(mlsgd_ctx* c, Plan* P) {
     fmg_start<double>(c, P);
 }
 
+// One scalar phase over every problem.  clear: the counter of active problems
+// is set to 0 for a later phase that counts them.
+void scalar_phase(mlsgd_ctx* c, Plan* P, int phase, bool sums, double rtol, bool count, bool clear,
+                  int aux = 0) {
+  cg_scalar(phase, P->d_scal, P->nprob, P->max_slots, P->d_poff, P->d_pcnt,
+            sums ? P->d_partial : nullptr, rtol, c->pb.max_iters, count ? c->d_count : nullptr,
+            clear ? c->d_count : nullptr, c->stream, aux);
+}
+
 // One Krylov step of every active problem after z = M r: p = z + beta p,
 // q = A p and alpha, then r -= alpha q with <r, r>.  With xdefer the step
 // x += alpha p is applied by the next iteration's matvec, which reads that p
@@ -1112,8 +1123,6 @@ void fmg(mlsgd_ctx* c, Plan* P) {
 // modes: the same x + alpha p is formed, one pass later.
 void krylov_step(mlsgd_ctx* c, Plan* P, bool mg, int it) {
   hipStream_t s = c->stream;
-  const double rtol = c->pb.rtol;
-  const int maxit = c->pb.max_iters;
   const bool defer = c->xdefer;
   int pslot = 0;  // every group writes the new direction into p[pcur ^ 1]
   for (auto& gr : P->groups) {
@@ -1133,8 +1142,7 @@ void krylov_step(mlsgd_ctx* c, Plan* P, bool mg, int it) {
     }, 4);
     pslot = gr.pcur ^ 1;
   }
-  cg_scalar(PH_ALPHA, P->d_scal, P->nprob, P->d_poff, P->d_pcnt, P->d_partial, rtol, maxit,
-            nullptr, s, pslot);
+  scalar_phase(c, P, PH_ALPHA, true, c->pb.rtol, false, true, pslot);
   for (auto& gr : P->groups) {
     GridArgs g = args_group(c, P, gr, true);
     float* r32 = (mg && c->mixed) ? P->sizes[gr.sl].Bf + (size_t)gr.p0 * srow(gr.n) : nullptr;
@@ -1172,8 +1180,7 @@ void krylov(mlsgd_ctx* c, Plan* P, int* iters_out, int* nonconv_out, double* rel
       group_dot(g, r, r, P->d_poff, P->d_partial, s);
     }
   }
-  cg_scalar(PH_INIT_BB, P->d_scal, P->nprob, P->d_poff, P->d_pcnt, P->d_partial, rtol, maxit,
-            nullptr, s);
+  scalar_phase(c, P, PH_INIT_BB, true, rtol, false, false);
   fmg(c, P);
   // after a full-multigrid start r0 carries the evaluation error of b - A x0
   // (near the FP64 residual floor, about 0.3 rtol on 129^3 grids), which the
@@ -1191,11 +1198,9 @@ void krylov(mlsgd_ctx* c, Plan* P, int* iters_out, int* nonconv_out, double* rel
     }
     if (mg) {
       precondition(c, P);
-      cg_scalar(PH_RZ0, P->d_scal, P->nprob, P->d_poff, P->d_pcnt, P->d_partial, rtol, maxit,
-                nullptr, s);
+      scalar_phase(c, P, PH_RZ0, true, rtol, false, false);
     } else {
-      cg_scalar(PH_RZ0_RR, P->d_scal, P->nprob, P->d_poff, P->d_pcnt, nullptr, rtol, maxit,
-                nullptr, s);
+      scalar_phase(c, P, PH_RZ0_RR, false, rtol, false, false);
     }
     // the first quiet iterations run without a host read of the active
     // count: a problem that converged there is inactive and skipped, so at
@@ -1204,17 +1209,14 @@ void krylov(mlsgd_ctx* c, Plan* P, int* iters_out, int* nonconv_out, double* rel
     for (int it = 0; it < maxit; ++it) {
       krylov_step(c, P, mg, it);
       const bool read = it + 1 > quiet;
-      cg_scalar(PH_RR, P->d_scal, P->nprob, P->d_poff, P->d_pcnt, P->d_partial, rtol_rr, maxit,
-                read ? c->d_count : nullptr, s);
+      scalar_phase(c, P, PH_RR, true, rtol_rr, read, false);
       HIPCHK(hipGetLastError());
       if (read && read_count(c) == 0) break;
       if (mg) {
         precondition(c, P);
-        cg_scalar(PH_RZ, P->d_scal, P->nprob, P->d_poff, P->d_pcnt, P->d_partial, rtol, maxit,
-                  nullptr, s);
+        scalar_phase(c, P, PH_RZ, true, rtol, false, false);
       } else {
-        cg_scalar(PH_RZ_RR, P->d_scal, P->nprob, P->d_poff, P->d_pcnt, nullptr, rtol, maxit,
-                  nullptr, s);
+        scalar_phase(c, P, PH_RZ_RR, false, rtol, false, false);
       }
     }
     // the norm of the true residual b0 - A x (not stored); restart the
@@ -1222,18 +1224,14 @@ void krylov(mlsgd_ctx* c, Plan* P, int* iters_out, int* nonconv_out, double* rel
     // checked again: the others were not touched, and their partial slots
     // still hold the last check's sums
     flush_steps(c, P);
-    if (restart > 0)
-      cg_scalar(PH_RECHECK, P->d_scal, P->nprob, P->d_poff, P->d_pcnt, nullptr, rtol, maxit,
-                nullptr, s);
+    if (restart > 0) scalar_phase(c, P, PH_RECHECK, false, rtol, false, false);
     for (auto& gr : P->groups)
       march_resid_norm(args_group(c, P, gr, restart > 0), gr.x, gr.b0, P->d_poff, P->d_partial,
                        s);
     const bool force = c->force_restart && restart == 0;
-    cg_scalar(PH_TRUE, P->d_scal, P->nprob, P->d_poff, P->d_pcnt, P->d_partial, rtol, maxit,
-              force ? nullptr : c->d_count, s);
-    if (force)
-      cg_scalar(PH_FORCE_RESTART, P->d_scal, P->nprob, P->d_poff, P->d_pcnt, nullptr, rtol, maxit,
-                c->d_count, s);
+    // (the counter is 0 here: the loop above ended on a count of 0)
+    scalar_phase(c, P, PH_TRUE, true, rtol, !force, false);
+    if (force) scalar_phase(c, P, PH_FORCE_RESTART, false, rtol, true, false);
     HIPCHK(hipGetLastError());
     if (read_count(c) == 0) break;
     // the restarted problems start again from r = b - A x
@@ -1264,10 +1262,9 @@ void krylov_fixed(mlsgd_ctx* c, Plan* P, int iters, int slot, bool bb_ready = fa
   hipStream_t s = c->stream;
   const bool mg = c->pb.solver == MLSGD_SOLVER_MGPCG;
   const double rtol = c->pb.rtol;
-  const int maxit = c->pb.max_iters;
   // the host reads no count here (the stats kernel reports the outcome)
-  auto cg = [&](int phase, const double* partial) {
-    cg_scalar(phase, P->d_scal, P->nprob, P->d_poff, P->d_pcnt, partial, rtol, maxit, nullptr, s);
+  auto cg = [&](int phase, bool sums) {
+    scalar_phase(c, P, phase, sums, rtol, false, false);
   };
   auto start = [&]() {  // z = M r and rz for the active problems
     if (mg && c->mixed) {
@@ -1279,21 +1276,20 @@ void krylov_fixed(mlsgd_ctx* c, Plan* P, int iters, int slot, bool bb_ready = fa
     }
     if (mg) {
       precondition(c, P);
-      cg(PH_RZ0, P->d_partial);
+      cg(PH_RZ0, true);
     } else {
-      cg(PH_RZ0_RR, nullptr);
+      cg(PH_RZ0_RR, false);
     }
   };
   auto iterate = [&](int count) {
     for (int it = 0; it < count; ++it) {
       krylov_step(c, P, mg, it);
-      cg_scalar(PH_RR, P->d_scal, P->nprob, P->d_poff, P->d_pcnt, P->d_partial,
-                fmg_applies(c, P) ? c->fmg_margin * rtol : rtol, maxit, nullptr, s);
+      scalar_phase(c, P, PH_RR, true, fmg_applies(c, P) ? c->fmg_margin * rtol : rtol, false, false);
       if (mg) {
         precondition(c, P);
-        cg(PH_RZ, P->d_partial);
+        cg(PH_RZ, true);
       } else {
-        cg(PH_RZ_RR, nullptr);
+        cg(PH_RZ_RR, false);
       }
     }
   };
@@ -1302,10 +1298,10 @@ void krylov_fixed(mlsgd_ctx* c, Plan* P, int iters, int slot, bool bb_ready = fa
   // slots still hold that check's sums, so PH_TRUE keeps their verdict
   auto true_residual = [&](bool recheck) {
     flush_steps(c, P);
-    if (recheck) cg(PH_RECHECK, nullptr);
+    if (recheck) cg(PH_RECHECK, false);
     for (auto& gr : P->groups)
       march_resid_norm(args_group(c, P, gr, recheck), gr.x, gr.b0, P->d_poff, P->d_partial, s);
-    cg(PH_TRUE, P->d_partial);
+    cg(PH_TRUE, true);
   };
   if (!bb_ready) {
     for (auto& gr : P->groups) {
@@ -1314,12 +1310,12 @@ void krylov_fixed(mlsgd_ctx* c, Plan* P, int iters, int slot, bool bb_ready = fa
       group_dot(g, r, r, P->d_poff, P->d_partial, s);
     }
   }
-  cg(PH_INIT_BB, P->d_partial);
+  cg(PH_INIT_BB, true);
   fmg(c, P);
   start();
   iterate(iters);
   true_residual(false);
-  if (c->force_restart) cg(PH_FORCE_RESTART, nullptr);
+  if (c->force_restart) cg(PH_FORCE_RESTART, false);
   // restart block: the problems that missed rtol start again from b - A x
   for (auto& gr : P->groups)
     march_resid<double>(args_group(c, P, gr, true), gr.x, gr.b0, rows_of(P->sizes[gr.sl].B, gr),
@@ -1376,7 +1372,7 @@ void state_phase(mlsgd_ctx* c, Plan* P, int* it, int* nc, double* rr, double* y_
     group_misfit(g, gr.x, c->yd_lvl[gr.n], b, P->d_poff, P->d_partial, s);
     copy_rows(gr.n, gr.count, b, gr.b0, s);
     const double h = 1.0 / (double)(gr.n - 1);
-    sum_partials(gr.count, P->d_poff + gr.p0, P->d_pcnt + gr.p0, P->d_partial, 0.5 * h * h * h,
+    sum_partials(gr.count, P->h_pcnt[gr.p0], P->d_poff + gr.p0, P->d_pcnt + gr.p0, P->d_partial, 0.5 * h * h * h,
                  P->d_phi + gr.p0, s);
   }
   HIPCHK(hipGetLastError());
