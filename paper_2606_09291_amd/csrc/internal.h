@@ -36,8 +36,9 @@ struct Tiling {
 };
 
 // tile_y: y extent of the tiles on grids with more than 32 interior points
-// (4, 8 or 16); xchunk: x planes per workgroup.
-Tiling make_tiling(int n, int tile_y, int xchunk);
+// (4, 8 or 16); xchunk: x planes per workgroup; rows: rows of the batch, for
+// which the chunk may be shortened (0: not).
+Tiling make_tiling(int n, int tile_y, int xchunk, int rows);
 
 // Per-problem state of the batched Krylov solves (all FP64).
 struct CgScal {

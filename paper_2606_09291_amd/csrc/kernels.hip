@@ -115,7 +115,34 @@ __device__ __forceinline__ double block_sum(double v, double* sred) {
 
 static inline int cdiv(long long a, long long b) { return (int)((a + b - 1) / b); }
 
-Tiling make_tiling(int n, int tile_y, int xchunk) {
+// A workgroup marches its chunk at about a memory round trip per plane, so a
+// batch too small to fill the chip takes as long as one chunk.  With the batch's
+// rows known, the chunk is halved (to even lengths >= 4) while that shortens the
+// estimate rounds x (planes + 6): rounds of the workgroups that fit at once, the
+// chunk's planes, and about six planes' worth of first loads and ring planes.  A
+// gain under 15% keeps the longer chunk (each chunk repeats two ring planes),
+// and grids of one 8 x 8 tile keep one chunk (k_vsmall writes their one slot).
+// Measured, 32-plane chunks against the rule: one 33^3 state and adjoint solve 4.1
+// -> 2.0 ms (post-smoothing 48 -> 14 us a pass), the 17^3..65^3 law workload 13.8
+// -> 6.5, 300 solves of 33^3..65^3 26.7 -> 23.7; full batches keep their chunks.
+static int split_chunk(const Tiling& t, int m, int rows) {
+  const int threads = t.TY * t.TZ;
+  const long long fit = 256LL * (threads >= 1024 ? 1 : 1024 / threads);
+  auto cost = [&](int ch) {
+    const long long wg = (long long)rows * t.nty * t.ntz * cdiv(m, ch);
+    return ((wg + fit - 1) / fit) * (ch + 6);
+  };
+  int best = t.xchunk;
+  // one chunk of an odd number of planes splits as the even length above it
+  for (int ch = (t.nxc == 1 ? t.xchunk + (t.xchunk & 1) : t.xchunk); ch % 4 == 0;) {
+    ch /= 2;
+    if (ch < 4) break;
+    if (100 * cost(ch) < 85 * cost(best)) best = ch;
+  }
+  return best;
+}
+
+Tiling make_tiling(int n, int tile_y, int xchunk, int rows) {
   const int m = n - 2;
   Tiling t;
   if (m <= 8) {
@@ -133,6 +160,10 @@ Tiling make_tiling(int n, int tile_y, int xchunk) {
   t.ntz = cdiv(m, t.TZ);
   t.xchunk = m <= xch ? m : xch;
   t.nxc = cdiv(m, t.xchunk);
+  if (rows > 0 && m > 8) {
+    t.xchunk = split_chunk(t, m, rows);
+    t.nxc = cdiv(m, t.xchunk);
+  }
   t.tiles_per_row = t.nty * t.ntz * t.nxc;
   return t;
 }

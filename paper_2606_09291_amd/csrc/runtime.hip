@@ -311,8 +311,9 @@ void evict_plans(mlsgd_ctx* c, size_t need) {
 
 // Host-side layout of a list of blocks (grid sizes non-increasing): problem
 // order, groups, the grid sizes of the hierarchy and the partial-sum slots.
-// Touches no device memory beyond the per-size cosine tables.
-void plan_layout(mlsgd_ctx* c, const std::vector<Block>& blocks, Plan* P) {
+// Touches no device memory beyond the per-size cosine tables.  split: short
+// x chunks where the batch leaves the chip idle (more partial-sum slots).
+void plan_layout(mlsgd_ctx* c, const std::vector<Block>& blocks, Plan* P, bool split = true) {
   long long np = 0;
   for (const auto& b : blocks) np += b.count;
   require(np > 0 && np < (1LL << 30), "problem count out of range");
@@ -341,13 +342,13 @@ void plan_layout(mlsgd_ctx* c, const std::vector<Block>& blocks, Plan* P) {
   for (int n = nmax;; n = (n - 1) / 2 + 1) {
     SizeLvl s;
     s.n = n;
-    s.t = make_tiling(n, c->tile_y, c->xchunk);
     int rows = 0, top = 0;
     for (int q = 0; q < P->nprob; ++q) {
       if (P->h_n[q] >= n) rows = q + 1;
       if (P->h_n[q] > n) top = q + 1;
     }
     s.rows = rows;
+    s.t = make_tiling(n, c->tile_y, c->xchunk, split ? rows : 0);
     s.top_begin = top;
     s.cosT = cos_for(c, n);
     P->sizes.push_back(s);
@@ -369,11 +370,13 @@ void plan_layout(mlsgd_ctx* c, const std::vector<Block>& blocks, Plan* P) {
   P->h_pcnt.resize(np);
   P->h_poff.resize(np);
   long long off = 0;
-  for (int q = 0; q < P->nprob; ++q) {
-    P->h_pcnt[q] = make_tiling(P->h_n[q], c->tile_y, c->xchunk).tiles_per_row;
-    P->h_poff[q] = (int)off;
-    off += P->h_pcnt[q];
-    P->max_slots = std::max(P->max_slots, P->h_pcnt[q]);
+  for (const auto& g : P->groups) {
+    const int slots = P->sizes[g.sl].t.tiles_per_row;
+    P->max_slots = std::max(P->max_slots, slots);
+    for (int q = g.p0; q < g.p0 + g.count; ++q, off += slots) {
+      P->h_pcnt[q] = slots;
+      P->h_poff[q] = (int)off;
+    }
   }
   require(off < (1LL << 31), "partial buffer too large");
   P->npartial = off;
@@ -2142,7 +2145,12 @@ int mlsgd_solve_state_adjoint_noalloc(mlsgd_ctx* c, int level, int coarse, int64
     std::vector<Block> b{Block{n, level, first, count}};
     Plan T;   // transient: never enters the plan cache
     plan_layout(c, b, &T);
-    const size_t need = plan_carve(c, &T, nullptr);
+    size_t need = plan_carve(c, &T, nullptr);
+    if (need > kScratchBytes) {   // without the slots of shortened chunks it may fit
+      T = Plan{};
+      plan_layout(c, b, &T, false);
+      need = plan_carve(c, &T, nullptr);
+    }
     if (scratch_bytes) *scratch_bytes = (int64_t)need;
     if (need > kScratchBytes)
       throw Fail{MLSGD_EINVAL, "the batch needs " + std::to_string(need) +
