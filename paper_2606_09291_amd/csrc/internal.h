@@ -152,6 +152,14 @@ void vcycle_small(int rows, const double* om, int deg, int top_begin, const CgSc
                   const T* b9, const void* c9, const void* c5, const void* c3, int cache_bf16,
                   T* xout, const int* poff, double* partial, hipStream_t s);
 
+// Whole unpreconditioned CG solves, one workgroup each, of `rows` problems on an
+// n^3 grid (n <= CG_SMALL_MAX) with the cached FP64 1/a: right-hand-side rows
+// in, solution rows out (interior vertices), and the problems' scalars
+// [row0, row0 + rows) as the batched iteration leaves them.
+constexpr int CG_SMALL_MAX = 17;
+void cg_small(int n, int rows, int row0, CgScal* scal, const double* cache, const double* rhs,
+              double* x, double rtol, int max_iters, hipStream_t s);
+
 // ---- batched grid transfers (rows of one grid size) ----
 template <typename T>
 void restrict_rows(int nf, int rows, int row0, const CgScal* scal, const T* fine,

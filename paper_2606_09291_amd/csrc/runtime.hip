@@ -1168,6 +1168,25 @@ void flush_steps(mlsgd_ctx* c, Plan* P) {
   }
 }
 
+// Plain CG where every top grid is small enough for one workgroup: whole
+// solves as one launch per grid size, no host reads.  The event timing of the
+// matvec and the forced restarts are the level-by-level path's.
+bool cg_small_applies(const mlsgd_ctx* c, const Plan* P) {
+  if (c->pb.solver != MLSGD_SOLVER_CG || c->tm.on || c->force_restart) return false;
+  for (const auto& gr : P->groups)
+    if (gr.n > CG_SMALL_MAX || !P->sizes[gr.sl].C) return false;
+  return true;
+}
+
+void cg_small_solves(mlsgd_ctx* c, Plan* P) {
+  for (const auto& gr : P->groups) {
+    const SizeLvl& L = P->sizes[gr.sl];
+    cg_small(gr.n, gr.count, gr.p0, P->d_scal, L.C, rows_of(L.B, gr), gr.x, c->pb.rtol,
+             c->pb.max_iters, c->stream);
+  }
+  HIPCHK(hipGetLastError());
+}
+
 // Batched (preconditioned) CG on every problem of the plan.  On entry the
 // B rows of each top grid hold the right-hand side b, b0 a copy of it, x = 0.
 void krylov(mlsgd_ctx* c, Plan* P, int* iters_out, int* nonconv_out, double* relres_out,
@@ -1176,14 +1195,16 @@ void krylov(mlsgd_ctx* c, Plan* P, int* iters_out, int* nonconv_out, double* rel
   const bool mg = c->pb.solver == MLSGD_SOLVER_MGPCG;
   const double rtol = c->pb.rtol;
   const int maxit = c->pb.max_iters;
-  if (!bb_ready) {
+  const bool whole = cg_small_applies(c, P);
+  if (whole) cg_small_solves(c, P);
+  if (!bb_ready && !whole) {
     for (auto& gr : P->groups) {
       GridArgs g = args_group(c, P, gr, false);
       double* r = rows_of(P->sizes[gr.sl].B, gr);
       group_dot(g, r, r, P->d_poff, P->d_partial, s);
     }
   }
-  scalar_phase(c, P, PH_INIT_BB, true, rtol, false, false);
+  if (!whole) scalar_phase(c, P, PH_INIT_BB, true, rtol, false, false);
   fmg(c, P);
   // after a full-multigrid start r0 carries the evaluation error of b - A x0
   // (near the FP64 residual floor, about 0.3 rtol on 129^3 grids), which the
@@ -1191,7 +1212,7 @@ void krylov(mlsgd_ctx* c, Plan* P, int* iters_out, int* nonconv_out, double* rel
   // true-residual check at exit (still against rtol) rarely has to restart a
   // solve
   const double rtol_rr = fmg_applies(c, P) ? c->fmg_margin * rtol : rtol;
-  for (int restart = 0; restart < 3; ++restart) {
+  for (int restart = 0; restart < 3 && !whole; ++restart) {
     if (mg && c->mixed) {
       for (auto& gr : P->groups) {
         SizeLvl& L = P->sizes[gr.sl];
@@ -1306,6 +1327,13 @@ void krylov_fixed(mlsgd_ctx* c, Plan* P, int iters, int slot, bool bb_ready = fa
       march_resid_norm(args_group(c, P, gr, recheck), gr.x, gr.b0, P->d_poff, P->d_partial, s);
     cg(PH_TRUE, true);
   };
+  if (cg_small_applies(c, P)) {
+    cg_small_solves(c, P);
+    scal_to_stats(P->d_scal, P->nprob, rtol, &c->d_stat[slot].iters, &c->d_stat[slot].nonconv,
+                  &c->d_stat[slot].relres, s);
+    HIPCHK(hipGetLastError());
+    return;
+  }
   if (!bb_ready) {
     for (auto& gr : P->groups) {
       GridArgs g = args_group(c, P, gr, false);
@@ -1352,12 +1380,14 @@ void state_phase(mlsgd_ctx* c, Plan* P, int* it, int* nc, double* rr, double* y_
   // Every problem of a group has the same right-hand side, so |b|^2 is
   // summed over the group's first row and its partial slots copied to the
   // others.
-  const bool clear = !fmg_applies(c, P);
+  // (The whole-solve CG kernel sums it itself.)
+  const bool clear = !fmg_applies(c, P), whole = cg_small_applies(c, P);
   for (auto& gr : P->groups) {
     double* b = rows_of(P->sizes[gr.sl].B, gr);
     rows_broadcast(gr.n, gr.count, c->rhs_lvl[gr.n], b, s);
     rows_broadcast(gr.n, gr.count, c->rhs_lvl[gr.n], gr.b0, s);
     if (clear) rows_zero((long long)gr.count * srow(gr.n), gr.x, s);
+    if (whole) continue;
     GridArgs g1 = args_group(c, P, gr, false);
     g1.rows = 1;
     group_dot(g1, b, b, P->d_poff, P->d_partial, s);
