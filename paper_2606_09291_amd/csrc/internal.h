@@ -40,6 +40,20 @@ struct Tiling {
 // which the chunk may be shortened (0: not).
 Tiling make_tiling(int n, int tile_y, int xchunk, int rows);
 
+// Tiling of one grid size for the vector smoothing passes: a workgroup of R x LZ
+// threads, thread (r, l) owning 16 bytes of z line r, marches xchunk planes.
+struct VTile {
+  int R = 0, LZ = 0;   // rows and vectors per z line; R = 0: no vector form
+  int full = 0;        // the rows are the grid's whole y extent
+  int nty = 0, xchunk = 0, tiles = 0;
+  int PZ = 0;          // LDS elements per row
+  int cyn = 0, czn = 0;   // coarse footprint
+  int lds = 0;         // bytes of dynamic LDS
+};
+// elem: bytes of a value; tile_y, xchunk and rows as for make_tiling (the chunk
+// may also become longer than xchunk)
+VTile make_vtile(int n, int elem, int tile_y, int xchunk, int rows);
+
 // Per-problem state of the batched Krylov solves (all FP64).
 struct CgScal {
   double rz;      // <r, z> of the current iterate
@@ -69,6 +83,7 @@ struct GridArgs {
   const void* cache;    // [problem][n^3] cached 1/a of the compute type, or null
   int cache_bf16;       // FP32 sweeps: the cache holds bfloat16 values
   double omega1;        // first step of the fused two-step Jacobi sweep
+  VTile v;              // tiles of the vector smoothing passes
 };
 
 // ---- stencil kernels (marching LDS tiles, coefficient regenerated) ----
@@ -108,14 +123,15 @@ void dinv_rows(int n, int rows, const void* cache, int cache_bf16, T* dinv, hipS
 template <typename T>
 void march_jac2z(const GridArgs& g, const T* dinv, const T* b, T* xout, double omega1,
                  double omega2, hipStream_t s);
-// the fused smoothing passes below serve the 8x64, 16x64, 8x32 and 16x16
-// tiles (grids of 17 and more vertices, tile height 4 excepted) with a cached
-// coefficient
+// The fused smoothing passes below serve grids with a cached coefficient: in
+// their vector form where g.v has one, otherwise (lines of over 64 vectors; 11
+// and 15 vertices in FP32) in their scalar form on 8x64, 16x64 and 16x16 tiles.
 inline bool fused_tiles(const GridArgs& g) {
-  return g.cache != nullptr && ((g.t.TZ == 64 && g.t.TY >= 8) || g.t.TZ == 32 || g.t.TZ == 16);
+  return g.cache != nullptr && (g.v.R > 0 || (g.t.TZ == 64 && g.t.TY >= 8) || g.t.TZ == 16);
 }
 // the x chunks of g start on odd planes (one chunk, or chunks of even length)
 inline bool pre2r_half_tiles(const GridArgs& g) {
+  if (g.v.R > 0) return g.v.xchunk >= g.n - 2 || (g.v.xchunk & 1) == 0;
   return g.t.nxc == 1 || (g.t.xchunk & 1) == 0;
 }
 // the same two steps and the residual of their result in one pass:

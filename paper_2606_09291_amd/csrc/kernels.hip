@@ -992,43 +992,6 @@ __global__ void __launch_bounds__(TY* TZ)
   }
 }
 
-template <typename T>
-bool march_pre2r(const GridArgs& g, const T* dinv, const T* b, T* xout, T* rout, double omega1,
-                 double omega2, bool half, hipStream_t s) {
-  if (!fused_tiles(g) || (half && !pre2r_half_tiles(g))) return false;
-  if (g.rows <= 0) return true;
-  const int nblk = g.rows * g.t.tiles_per_row;
-#define MLSGD_LAUNCH(TY_, TZ_, CK_, RH_)                                                     \
-  hipLaunchKernelGGL((k_pre2r<T, TY_, TZ_, CK_, RH_>), dim3(nblk), dim3(TY_ * TZ_), 0, s, g, \
-                     dinv, b, xout, rout, (T)omega1, (T)omega2)
-#define MLSGD_LAUNCH2(TY_, TZ_)         \
-  if (b16 && half)                      \
-    MLSGD_LAUNCH(TY_, TZ_, 2, true);    \
-  else if (b16)                         \
-    MLSGD_LAUNCH(TY_, TZ_, 2, false);   \
-  else if (half)                        \
-    MLSGD_LAUNCH(TY_, TZ_, 1, true);    \
-  else                                  \
-    MLSGD_LAUNCH(TY_, TZ_, 1, false)
-  const bool b16 = sizeof(T) == 4 && g.cache_bf16;
-  if (g.t.TZ == 16) {
-    MLSGD_LAUNCH2(16, 16);
-  } else if (g.t.TZ == 32) {
-    MLSGD_LAUNCH2(8, 32);
-  } else if (g.t.TY == 8) {
-    MLSGD_LAUNCH2(8, 64);
-  } else {
-    MLSGD_LAUNCH2(16, 64);
-  }
-#undef MLSGD_LAUNCH2
-#undef MLSGD_LAUNCH
-  return true;
-}
-template bool march_pre2r<double>(const GridArgs&, const double*, const double*, double*,
-                                  double*, double, double, bool, hipStream_t);
-template bool march_pre2r<float>(const GridArgs&, const float*, const float*, float*, float*,
-                                 double, double, bool, hipStream_t);
-
 // ---------------------------------------------------------------------------
 // Fused post-smoothing: two Chebyshev steps after the coarse-grid correction
 // in one pass,
@@ -1382,12 +1345,659 @@ __global__ void __launch_bounds__(TY* TZ)
   }
 }
 
+// ---------------------------------------------------------------------------
+// Vector form of the two fused smoothing passes (k_pre2v, k_post2v), for grids
+// of 11 and more vertices whose z line is at most 64 vectors of 16 bytes long.
+//
+// What bounds it: memory latency and LDS, not arithmetic.  The scalar form
+// (k_pre2r, k_post2: one point per lane on an 8 x 64 patch, y and z neighbours
+// through LDS) issued about 220 VALU and 40 LDS instructions per 64 points and
+// reached 3.0-3.4 TB/s of the bytes it needs in FP64 and 2.1-2.6 in FP32.  Here
+// a lane owns V = 2 (FP64) or 4 (FP32) consecutive z points of one row: loads
+// and stores are 16 bytes a lane, half or three quarters of the z neighbours
+// are the lane's own, and a workgroup holds whole z lines, so the rings exist
+// in y alone.  That is about 175 VALU and 15-20 LDS instructions per 128 (FP64)
+// or 256 (FP32) points.  One barrier a plane: the planes in LDS are double
+// buffered.
+//
+// A workgroup forms the middle stage on R rows (thread = row x lane) and the
+// output on the R - 2 inner ones; the first and last row's threads also load
+// the row beyond theirs.  Where a grid's whole plane fits 512 threads the tile
+// covers it (full) and nothing is formed twice.  Otherwise R is what fills 256
+// threads (three workgroups per CU at 150 VGPRs), and 10 for lines of more than
+// 32 vectors, whose chunk then spans the whole line if that still gives every
+// CU a workgroup (make_vtile).
+//
+// The harmonic faces are formed without their factor 2, which the scale 2 h^-2
+// takes over, and a step is x + omega (D^-1 (b / (2 h^-2) + sum of faces times
+// neighbours) - x): the scalar passes' steps up to rounding.
+//
+// Measured on synthetic rows, scalar against vector form, microseconds a pass
+// (post-smoothing / pre-smoothing): FP64 16 x 129^3 355/371 -> 272/258,
+// 96 x 65^3 264/256 -> 219/221, 416 x 33^3 161/142 -> 121/128, 1696 x 17^3
+// 76/56 -> 59/59; FP32 211/187 -> 146/146, 156/132 -> 111/111, 95/63 -> 51/51,
+// 49/33 -> 32/30, 4 x 257^3 415/388 -> 277/264, 70 x 49^3 90/66 -> 39/36; FP32
+// with the bfloat16 cache 266/248 -> 170/170 (129^3), 190/155 -> 131/115 (65^3).
+// Whole estimates 9^3..129^3: FP64 63.2 -> 58.5 ms, FP32 cycles 52.2 -> 48.1,
+// bfloat16 cache 62.3 -> 55.4; 9^3..257^3 with FP32 cycles 160 -> 147.
+// ---------------------------------------------------------------------------
+template <typename T>
+struct VecOf {
+  static constexpr int V = 16 / (int)sizeof(T);
+  typedef T type __attribute__((ext_vector_type(16 / sizeof(T))));
+  typedef type utype __attribute__((aligned(sizeof(T))));   // as it lies in memory
+};
+
+VTile make_vtile(int n, int elem, int tile_y, int xchunk, int rows) {
+  VTile v{};
+  const int V = 16 / elem, m = n - 2;
+  // lines that are no whole number of vectors (11 and 15 vertices in FP32) or
+  // longer than 64 of them, 9^3 and below (k_vsmall) and the 4 x 64 tiles
+  // (which keep the separate passes) have no vector form
+  if (m <= 8 || (n - 1) % V || (n - 1) / V > 64 || (m > 32 && tile_y == 4)) return v;
+  v.LZ = (n - 1) / V;
+  v.full = m * v.LZ <= 512;
+  v.R = v.full ? m : v.LZ > 32 ? 10 : (256 / v.LZ) & ~1;
+  v.nty = v.full ? 1 : cdiv(m, v.R - 2);
+  v.PZ = V * (v.LZ + 1);
+  v.cyn = v.R / 2 + 3;
+  v.czn = (n - 1) / 2 + 1;
+  const int threads = v.R * v.LZ;
+  v.lds = (6 * (v.R + 2) * v.PZ + 4 * v.cyn * v.czn + V) * elem;
+  // The chunk: as split_chunk, but also longer than the given one, up to the
+  // whole line.  Odd chunk lengths stay as given (the x-restricted residual
+  // needs even ones).
+  int best = m <= xchunk ? m : xchunk;
+  if (rows > 0 && (m <= xchunk || xchunk % 2 == 0)) {
+    const long long fit = 256LL * max(1, 12 / cdiv(threads, 64));
+    auto cost = [&](int ch) {
+      const long long wg = (long long)rows * v.nty * cdiv(m, ch);
+      return ((wg + fit - 1) / fit) * (ch + 6);
+    };
+    int ch = m + (m & 1);
+    if (xchunk < m)
+      for (ch = xchunk; 2 * ch < m; ch *= 2) {}
+    best = m;
+    for (;; ch /= 2) {
+      if (ch < m && cost(ch) < cost(best)) best = ch;
+      if (ch % 4 || ch / 2 < 4) break;
+    }
+  }
+  v.xchunk = best;
+  v.tiles = v.nty * cdiv(m, best);
+  return v;
+}
+
+// Geometry of one workgroup of the vector passes and its loads.  A value of
+// plane ix is addressed by a scalar base and the lane's 32-bit byte offset;
+// rows and planes beyond the grid read the nearest one inside (their values
+// only reach results that are set to zero or discarded).
+template <typename T, int CK>
+struct VGeo {
+  static constexpr int V = VecOf<T>::V;
+  using VT = typename VecOf<T>::type;
+  using VU = typename VecOf<T>::utype;
+  static constexpr uint32_t CS = CK == 2 ? 2 : sizeof(T);   // bytes of a cached coefficient
+  int n, tile, prob, r, l, j, jb, js;
+  int x0, x1, o, so, rows2;   // LDS: own and secondary slot, elements of one plane of R + 2 rows
+  bool rint, out, edge, first, s_on, idle;
+  size_t base;
+  uint32_t pstr, eo, es;      // plane stride, element offsets of the own and the secondary row
+  const char* cache;
+  __device__ int clampj(int a) const { return min(max(a, 0), n - 1); }
+  __device__ void init(const GridArgs& g) {
+    n = g.n;
+    const int LP = lay_pitch(n), LO = lay_off(n);
+    const int bid = xcd_swizzle(blockIdx.x, gridDim.x);
+    const int row = bid / g.v.tiles;
+    tile = bid - row * g.v.tiles;
+    prob = g.row0 + row;
+    idle = g.scal && !g.scal[prob].active;   // uniform
+    const int ty = tile % g.v.nty, xc = tile / g.v.nty;
+    r = threadIdx.x / g.v.LZ;
+    l = threadIdx.x - r * g.v.LZ;
+    jb = g.v.full ? 1 : ty * (g.v.R - 2);
+    j = jb + r;
+    rint = j >= 1 && j <= n - 2;
+    out = rint && (g.v.full || (r >= 1 && r <= g.v.R - 2));
+    edge = l == g.v.LZ - 1;
+    first = l == 0;
+    s_on = r == 0 || r == g.v.R - 1;
+    js = r == 0 ? j - 1 : j + 1;
+    rows2 = (g.v.R + 2) * g.v.PZ;
+    o = (r + 1) * g.v.PZ + V * (l + 1);
+    so = (r == 0 ? 0 : g.v.R + 1) * g.v.PZ + V * (l + 1);
+    base = (size_t)row * (size_t)g.stride;
+    pstr = (uint32_t)n * (uint32_t)LP;
+    eo = (uint32_t)(clampj(j) * LP + 1 + V * l + LO);
+    es = (uint32_t)(clampj(js) * LP + 1 + V * l + LO);
+    cache = (const char*)g.cache + (size_t)prob * (size_t)g.stride * CS;
+    x0 = 1 + xc * g.v.xchunk;
+    x1 = min(x0 + g.v.xchunk, n - 1);
+  }
+  __device__ size_t plane(int ix) const { return (size_t)clampj(ix) * pstr; }   // uniform
+  __device__ VT load(const T* p, int ix, uint32_t e) const {
+    return *(const VU*)((const char*)(p + plane(ix)) + e * (uint32_t)sizeof(T));
+  }
+  __device__ void store(T* p, int ix, const VT& v) const {
+    __builtin_nontemporal_store(v, (VU*)((char*)(p + base + (size_t)ix * pstr) + eo * (uint32_t)sizeof(T)));
+  }
+  __device__ VT load_a(int ix, uint32_t e) const {   // 1/a
+    const char* p = cache + plane(ix) * CS + e * CS;
+    if constexpr (CK == 2) {
+      typedef uint16_t u16x4 __attribute__((ext_vector_type(4), aligned(2)));
+      const u16x4 h = *(const u16x4*)p;
+      VT v;
+#pragma unroll
+      for (int k = 0; k < 4; ++k) v[k] = from_bf16(h[k]);
+      return v;
+    } else {
+      return *(const VU*)p;
+    }
+  }
+  __device__ T load_a0(int ix) const {   // 1/a at z = 0, left of the row's first vector
+    const char* p = cache + plane(ix) * CS + (eo - 1) * CS;
+    if constexpr (CK == 2)
+      return (T)from_bf16(*(const uint16_t*)p);
+    else
+      return *(const T*)p;
+  }
+  __device__ static VT fill(T a) {
+    VT v;
+#pragma unroll
+    for (int e = 0; e < V; ++e) v[e] = a;
+    return v;
+  }
+  // half the harmonic faces between two vectors of 1/a
+  __device__ static VT face2(const VT& a, const VT& b) {
+    VT v;
+#pragma unroll
+    for (int e = 0; e < V; ++e) v[e] = srcp((T)(a[e] + b[e]));
+    return v;
+  }
+};
+
+// half faces of a row's vector to its z neighbours (a: the row in LDS at o)
+template <typename T, typename VT>
+__device__ __forceinline__ void zfaces(const T* a, int o, const VT& ac, T (&fz)[VecOf<T>::V + 1]) {
+  constexpr int V = VecOf<T>::V;
+  fz[0] = srcp((T)(a[o - 1] + ac[0]));
+#pragma unroll
+  for (int e = 1; e < V; ++e) fz[e] = srcp((T)(ac[e - 1] + ac[e]));
+  fz[V] = srcp((T)(ac[V - 1] + a[o + V]));
+}
+// of + the y and z terms of the stencil at row slot o of t (own values v)
+template <typename T, typename VT>
+__device__ __forceinline__ VT yz_terms(VT of, const T* t, int o, int PZ, const VT& v, const VT& fym,
+                                       const VT& fyp, const T (&fz)[VecOf<T>::V + 1]) {
+  constexpr int V = VecOf<T>::V;
+  const VT tym = *(const VT*)(t + o - PZ), typ = *(const VT*)(t + o + PZ);
+  const T tl = t[o - 1], tr = t[o + V];
+#pragma unroll
+  for (int e = 0; e < V; ++e) {
+    T s = of[e];
+    s += fym[e] * tym[e];
+    s += fyp[e] * typ[e];
+    s += fz[e] * (e > 0 ? v[e > 0 ? e - 1 : 0] : tl);
+    s += fz[e + 1] * (e < V - 1 ? v[e < V - 1 ? e + 1 : 0] : tr);
+    of[e] = s;
+  }
+  return of;
+}
+
+// Zero column z = 0 of the two value arrays and the rows beyond the tile of the
+// second one (read by discarded rows only).
+template <typename T, int CK>
+__device__ __forceinline__ void vec_lds_init(const VGeo<T, CK>& G, T* sy, T* s3) {
+  if (G.first) {
+#pragma unroll
+    for (int b = 0; b < 2; ++b) {
+      sy[b * G.rows2 + G.o - 1] = T(0);
+      s3[b * G.rows2 + G.o - 1] = T(0);
+    }
+  }
+  if (G.s_on) {
+#pragma unroll
+    for (int b = 0; b < 2; ++b)
+      *(typename VecOf<T>::type*)(s3 + b * G.rows2 + G.so) = VGeo<T, CK>::fill(T(0));
+  }
+}
+
+constexpr int VEC_THREADS = 640;   // most threads of a tile (R = 10, 64 vectors)
+
+// Two Chebyshev steps from x = 0 and the residual (k_pre2r's pass; RH: its x
+// part restricted along x).  In step q the middle stage x2 of plane q and the
+// residual of plane q - 1 are formed; planes q + 2 of b, 1/D and 1/a load
+// meanwhile.
+template <typename T, int CK, bool RH>
+__global__ void __launch_bounds__(VEC_THREADS)
+    k_pre2v(GridArgs g, const T* __restrict__ dinv, const T* __restrict__ rhs,
+            T* __restrict__ xout, T* __restrict__ rout, T omega1, T omega2) {
+  using Geo = VGeo<T, CK>;
+  using VT = typename Geo::VT;
+  constexpr int V = Geo::V;
+  extern __shared__ __align__(16) unsigned char smem[];
+  Geo G;
+  G.init(g);
+  if (G.idle) return;
+  const int n = G.n, PZ = g.v.PZ, o = G.o, x0 = G.x0, x1 = G.x1;
+  T* const sy = (T*)smem;            // x1 of planes q and q - 1
+  T* const sa = sy + 2 * G.rows2;    // 1/a
+  T* const s3 = sa + 2 * G.rows2;    // x2 of planes q - 1 and q - 2
+  vec_lds_init(G, sy, s3);
+  const T* __restrict__ brow = rhs + G.base;
+  const T* __restrict__ drow = dinv + G.base;
+  const VT zero = Geo::fill(T(0));
+  const int qend = RH ? min(x1 + 1, n - 1) : x1;
+  const T i2 = T(2) * (T)g.ih2, kk = T(1) / i2;
+  // state on entry to step q: x1 and 1/a of planes q and q + 1, b of both, the
+  // b and x- terms of x2 on plane q (S1) and of the residual on q - 1 (S2), x2
+  // of plane q - 1 with its y and z faces and diagonal, the face q - 1 | q
+  VT yc, yn, S1, fxm, ac, an, bc, bn;
+  VT S2 = zero, x2p = zero, dg2 = zero, fym2 = zero, fyp2 = zero, hacc = zero;
+  T fz2[V + 1];
+#pragma unroll
+  for (int e = 0; e <= V; ++e) fz2[e] = T(0);
+  VT sys = zero, sas = Geo::fill(T(1));
+  T a0c = T(1);
+  {
+    const int q = x0 - 1;
+    const VT am = G.load_a(q - 1, G.eo);
+    ac = G.load_a(q, G.eo);
+    an = G.load_a(q + 1, G.eo);
+    const VT ym = (omega1 * G.load(brow, q - 1, G.eo)) * G.load(drow, q - 1, G.eo);
+    bc = G.load(brow, q, G.eo);
+    yc = (omega1 * bc) * G.load(drow, q, G.eo);
+    bn = G.load(brow, q + 1, G.eo);
+    yn = (omega1 * bn) * G.load(drow, q + 1, G.eo);
+    if (G.first) a0c = G.load_a0(q);
+    fxm = Geo::face2(am, ac);
+    S1 = kk * bc + (q >= 1 ? fxm * ym : zero);
+    if (G.s_on) {
+      sys = (omega1 * G.load(brow, q, G.es)) * G.load(drow, q, G.es);
+      sas = G.load_a(q, G.es);
+    }
+  }
+
+  for (int q = x0 - 1; q <= qend; ++q) {
+    const VT rb = G.load(brow, q + 2, G.eo);
+    const VT rd = G.load(drow, q + 2, G.eo);
+    const VT ra = G.load_a(q + 2, G.eo);
+    T ra0 = T(1);
+    if (G.first) ra0 = G.load_a0(q + 1);
+    VT rsb = zero, rsd = zero, rsa = zero;
+    if (G.s_on) {
+      rsb = G.load(brow, q + 1, G.es);
+      rsd = G.load(drow, q + 1, G.es);
+      rsa = G.load_a(q + 1, G.es);
+    }
+    T* const y_ = sy + (q & 1) * G.rows2;
+    T* const a_ = sa + (q & 1) * G.rows2;
+    T* const t_ = s3 + (q & 1) * G.rows2;
+    *(VT*)(y_ + o) = yc;
+    *(VT*)(a_ + o) = ac;
+    *(VT*)(t_ + o) = x2p;
+    if (G.first) a_[o - 1] = a0c;
+    if (G.s_on) {
+      *(VT*)(y_ + G.so) = sys;
+      *(VT*)(a_ + G.so) = sas;
+    }
+    __syncthreads();
+
+    const VT fxp = Geo::face2(ac, an);
+    const VT fym = Geo::face2(ac, *(const VT*)(a_ + o - PZ));
+    const VT fyp = Geo::face2(ac, *(const VT*)(a_ + o + PZ));
+    T fz[V + 1];
+    zfaces<T, VT>(a_, o, ac, fz);
+    const VT of = yz_terms<T, VT>(S1 + fxp * yn, y_, o, PZ, yc, fym, fyp, fz);
+    VT dg, x2;
+#pragma unroll
+    for (int e = 0; e < V; ++e) {
+      dg[e] = ((fxm[e] + fxp[e]) + (fym[e] + fyp[e])) + (fz[e] + fz[e + 1]);
+      x2[e] = yc[e] + omega2 * (of[e] * srcp(dg[e]) - yc[e]);
+    }
+    if (!(q >= 1 && q <= n - 2 && G.rint)) x2 = zero;
+    if (G.edge) x2[V - 1] = T(0);   // z = n - 1
+
+    const int qr = q - 1;
+    if (qr >= x0 && G.out) {
+      const VT o2 = yz_terms<T, VT>(S2 + fxm * x2, t_, o, PZ, x2p, fym2, fyp2, fz2);
+      VT rv = i2 * (o2 - dg2 * x2p);
+      if (G.edge) rv[V - 1] = T(0);
+      if constexpr (RH) {
+        if (qr < x1) G.store(xout, qr, x2p);
+        if (qr & 1) {
+          // r(qr) closes coarse plane (qr - 1) / 2 and opens (qr + 1) / 2
+          if (qr >= x0 + 2) G.store(rout, (qr - 1) >> 1, hacc + T(0.25) * rv);
+          hacc = T(0.25) * rv;
+        } else {
+          hacc = hacc + T(0.5) * rv;
+        }
+      } else {
+        G.store(xout, qr, x2p);
+        G.store(rout, qr, rv);
+      }
+    }
+
+    S2 = kk * bc + fxm * x2p;
+    S1 = kk * bn + fxp * yc;
+    bc = bn;
+    bn = rb;
+    fym2 = fym; fyp2 = fyp; dg2 = dg; x2p = x2;
+#pragma unroll
+    for (int e = 0; e <= V; ++e) fz2[e] = fz[e];
+    fxm = fxp;
+    ac = an;
+    an = ra;
+    yc = yn;
+    yn = (omega1 * rb) * rd;
+    a0c = ra0;
+    if (G.s_on) {
+      sys = (omega1 * rsb) * rsd;
+      sas = rsa;
+    }
+  }
+}
+
+// Two Chebyshev steps after the coarse-grid correction (k_post2's pass; XZ: from
+// x = 0).  In step q the first step x3 of plane q and the second x4 of plane
+// q - 1 are formed.  The coarse planes of the tile's footprint sit in a
+// four-plane LDS ring; a row forms its correction of plane q + 2 from it.
+template <typename T, int CK, bool XZ>
+__global__ void __launch_bounds__(VEC_THREADS)
+    k_post2v(GridArgs g, const T* __restrict__ xin, const T* __restrict__ xc,
+             const T* __restrict__ rhs, T* __restrict__ xout, const int* __restrict__ poff,
+             double* __restrict__ partial, int top_begin, T omega_a, T omega_b) {
+  using Geo = VGeo<T, CK>;
+  using VT = typename Geo::VT;
+  constexpr int V = Geo::V;
+  extern __shared__ __align__(16) unsigned char smem[];
+  __shared__ double sred[VEC_THREADS / 64];
+  Geo G;
+  G.init(g);
+  if (G.idle) return;
+  const int n = G.n, PZ = g.v.PZ, o = G.o, x0 = G.x0, x1 = G.x1;
+  const int tid = threadIdx.x, NT = g.v.R * g.v.LZ;
+  T* const sy = (T*)smem;            // y of planes q and q - 1
+  T* const sa = sy + 2 * G.rows2;    // 1/a
+  T* const s3 = sa + 2 * G.rows2;    // x3 of planes q - 1 and q - 2
+  T* const scs = s3 + 2 * G.rows2;   // coarse plane J in slot J & 3
+  const T* __restrict__ xrow = XZ ? nullptr : xin + G.base;
+  const T* __restrict__ brow = rhs + G.base;
+  const VT zero = Geo::fill(T(0));
+  auto ldx = [&](int ix, uint32_t e) -> VT {
+    if constexpr (XZ)
+      return zero;
+    else
+      return G.load(xrow, ix, e);
+  };
+
+  // coarse ring: cyn rows from cy0 by the whole coarse line; a thread stages
+  // slots tid and tid + NT
+  const int nc = (n - 1) / 2 + 1, czn = g.v.czn, slab = g.v.cyn * czn;
+  const int cLP = lay_pitch(nc), cLO = lay_off(nc);
+  const T* __restrict__ crow = xc + (size_t)(G.base / (size_t)g.stride) * (size_t)lay_row(nc);
+  const int cy0 = max(G.jb - 1, 0) >> 1;
+  const size_t cpl = (size_t)nc * cLP;
+  auto slot = [&](int i, uint32_t& e) -> bool {
+    const int a = i / czn;
+    e = (uint32_t)((cy0 + a) * cLP + (i - a * czn) + cLO);
+    return i < slab && cy0 + a <= nc - 1;
+  };
+  uint32_t co0, co1;
+  const bool c0 = slot(tid, co0), c1 = slot(tid + NT, co1);
+  auto cload = [&](bool on, uint32_t e, int J) -> T {
+    return (on && J >= 0 && J <= nc - 1) ? crow[(size_t)J * cpl + e] : T(0);
+  };
+  auto cstore = [&](int J, T a, T b) {
+    T* s = scs + (J & 3) * slab;
+    if (tid < slab) s[tid] = a;
+    if (tid + NT < slab) s[tid + NT] = b;
+  };
+  // y-interpolated values of coarse plane J under a row, then the trilinear
+  // correction of its V points on plane ix
+  struct Line {
+    T w[V / 2 + 1];
+  };
+  auto line = [&](int J, int lc, int dy) -> Line {
+    const T* p = scs + (J & 3) * slab + lc;
+    Line c;
+#pragma unroll
+    for (int k = 0; k <= V / 2; ++k) c.w[k] = T(0.5) * (p[k] + p[k + dy]);
+    return c;
+  };
+  auto corr = [&](int ix, int lc, int dy) -> VT {
+    Line c = line(ix >> 1, lc, dy);
+    if (ix & 1) {   // uniform
+      const Line d = line((ix >> 1) + 1, lc, dy);
+#pragma unroll
+      for (int k = 0; k <= V / 2; ++k) c.w[k] = T(0.5) * (c.w[k] + d.w[k]);
+    }
+    VT y;
+#pragma unroll
+    for (int e = 0; e < V; e += 2) {
+      y[e] = T(0.5) * (c.w[e / 2] + c.w[e / 2 + 1]);
+      y[e + 1] = c.w[e / 2 + 1];
+    }
+    return y;
+  };
+  const int jc = G.clampj(G.j), jsc = G.clampj(G.js);
+  const int lcp = ((jc >> 1) - cy0) * czn + (V / 2) * G.l, dyp = (jc & 1) ? czn : 0;
+  const int lcs = ((jsc >> 1) - cy0) * czn + (V / 2) * G.l, dys = (jsc & 1) ? czn : 0;
+
+  const int ixs = x0 - 2;    // first plane whose y a row forms
+  int chi = (x0 + 1) >> 1;   // highest coarse plane stored
+  for (int J = ixs >> 1; J <= chi; ++J) cstore(J, cload(c0, co0, J), cload(c1, co1, J));
+  T cn0 = cload(c0, co0, chi + 1), cn1 = cload(c1, co1, chi + 1);
+  vec_lds_init(G, sy, s3);
+  __syncthreads();
+
+  const T kk = T(1) / (T(2) * (T)g.ih2);
+  // state on entry to step q: y and 1/a of planes q and q + 1, b of q - 1 and
+  // q, the b and x- terms of x3 on plane q (S1) and of x4 on q - 1 (S2), x3 of
+  // plane q - 1 with its y and z faces and reciprocal diagonal, the face
+  // q - 1 | q
+  VT yc, yn, S1, fxm, ac, an, bc;
+  VT bm = zero, S2 = zero, x3p = zero, rd2 = zero, fym2 = zero, fyp2 = zero;
+  T fz2[V + 1];
+#pragma unroll
+  for (int e = 0; e <= V; ++e) fz2[e] = T(0);
+  VT sys = zero, sas = Geo::fill(T(1));
+  T a0c = T(1);
+  {
+    const VT am = G.load_a(ixs, G.eo);
+    ac = G.load_a(ixs + 1, G.eo);
+    an = G.load_a(ixs + 2, G.eo);
+    const VT ym = ldx(ixs, G.eo) + corr(ixs, lcp, dyp);
+    yc = ldx(ixs + 1, G.eo) + corr(ixs + 1, lcp, dyp);
+    yn = ldx(ixs + 2, G.eo) + corr(ixs + 2, lcp, dyp);
+    bc = G.load(brow, ixs + 1, G.eo);
+    if (G.first) a0c = G.load_a0(ixs + 1);
+    fxm = Geo::face2(am, ac);
+    S1 = kk * bc + (ixs >= 0 ? fxm * ym : zero);
+    if (G.s_on) {
+      sys = ldx(ixs + 1, G.es) + corr(ixs + 1, lcs, dys);
+      sas = G.load_a(ixs + 1, G.es);
+    }
+  }
+  double dot = 0.0;
+  const bool want = partial != nullptr && G.prob >= top_begin;
+
+  for (int q = x0 - 1; q <= x1; ++q) {
+    const VT rx = ldx(q + 2, G.eo);
+    const VT ra = G.load_a(q + 2, G.eo);
+    const VT rb = G.load(brow, q + 1, G.eo);
+    T ra0 = T(1);
+    if (G.first) ra0 = G.load_a0(q + 1);
+    VT rsx = zero, rsa = zero;
+    if (G.s_on) {
+      rsx = ldx(q + 1, G.es);
+      rsa = G.load_a(q + 1, G.es);
+    }
+    if (((q + 3) >> 1) > chi) {
+      ++chi;
+      cstore(chi, cn0, cn1);
+      cn0 = cload(c0, co0, chi + 1);
+      cn1 = cload(c1, co1, chi + 1);
+    }
+    T* const y_ = sy + (q & 1) * G.rows2;
+    T* const a_ = sa + (q & 1) * G.rows2;
+    T* const t_ = s3 + (q & 1) * G.rows2;
+    *(VT*)(y_ + o) = yc;
+    *(VT*)(a_ + o) = ac;
+    *(VT*)(t_ + o) = x3p;
+    if (G.first) a_[o - 1] = a0c;
+    if (G.s_on) {
+      *(VT*)(y_ + G.so) = sys;
+      *(VT*)(a_ + G.so) = sas;
+    }
+    __syncthreads();
+
+    const VT fxp = Geo::face2(ac, an);
+    const VT fym = Geo::face2(ac, *(const VT*)(a_ + o - PZ));
+    const VT fyp = Geo::face2(ac, *(const VT*)(a_ + o + PZ));
+    T fz[V + 1];
+    zfaces<T, VT>(a_, o, ac, fz);
+    const VT of = yz_terms<T, VT>(S1 + fxp * yn, y_, o, PZ, yc, fym, fyp, fz);
+    VT rd, x3;
+#pragma unroll
+    for (int e = 0; e < V; ++e) {
+      rd[e] = srcp((T)(((fxm[e] + fxp[e]) + (fym[e] + fyp[e])) + (fz[e] + fz[e + 1])));
+      x3[e] = yc[e] + omega_a * (of[e] * rd[e] - yc[e]);
+    }
+    if (!(q >= 1 && q <= n - 2 && G.rint)) x3 = zero;
+    if (G.edge) x3[V - 1] = T(0);   // z = n - 1
+
+    if (q - 1 >= x0 && G.out) {
+      const VT o2 = yz_terms<T, VT>(S2 + fxm * x3, t_, o, PZ, x3p, fym2, fyp2, fz2);
+      VT v = x3p + omega_b * (o2 * rd2 - x3p);
+      if (G.edge) v[V - 1] = T(0);
+      G.store(xout, q - 1, v);
+      if (want) {
+#pragma unroll
+        for (int e = 0; e < V; ++e) dot += (double)bm[e] * (double)v[e];
+      }
+    }
+
+    S2 = kk * bc + fxm * x3p;
+    bm = bc;
+    bc = rb;
+    S1 = kk * rb + fxp * yc;
+    fym2 = fym; fyp2 = fyp; rd2 = rd; x3p = x3;
+#pragma unroll
+    for (int e = 0; e <= V; ++e) fz2[e] = fz[e];
+    fxm = fxp;
+    ac = an;
+    an = ra;
+    yc = yn;
+    yn = rx + corr(q + 2, lcp, dyp);
+    a0c = ra0;
+    if (G.s_on) {
+      sys = rsx + corr(q + 1, lcs, dys);
+      sas = rsa;
+    }
+  }
+  if (want) {
+    // the last wave may be partly filled: its missing lanes add nothing
+    const int lane = tid & 63, live = min(64, NT - (tid & ~63));
+#pragma unroll
+    for (int k = 32; k > 0; k >>= 1) {
+      const double t = __shfl_down(dot, k, 64);
+      if (lane + k < live) dot += t;
+    }
+    if (lane == 0) sred[tid >> 6] = dot;
+    __syncthreads();
+    if (tid == 0) {
+      double s = 0.0;
+      for (int w = 0; w < (NT + 63) >> 6; ++w) s += sred[w];
+      partial[poff[G.prob] + G.tile] = s;
+    }
+  }
+}
+
+template <typename T, int CK>
+static void launch_pre2v(const GridArgs& g, const T* dinv, const T* b, T* xout, T* rout,
+                         double omega1, double omega2, bool half, hipStream_t s) {
+  const dim3 grid(g.rows * g.v.tiles), block(g.v.R * g.v.LZ);
+  if (half)
+    hipLaunchKernelGGL((k_pre2v<T, CK, true>), grid, block, g.v.lds, s, g, dinv, b, xout, rout,
+                       (T)omega1, (T)omega2);
+  else
+    hipLaunchKernelGGL((k_pre2v<T, CK, false>), grid, block, g.v.lds, s, g, dinv, b, xout, rout,
+                       (T)omega1, (T)omega2);
+}
+template <typename T, int CK>
+static void launch_post2v(const GridArgs& g, const T* xin, const T* xc, const T* b, T* xout,
+                          double omega_a, double omega_b, const int* poff, double* partial,
+                          int top_begin, hipStream_t s) {
+  const dim3 grid(g.rows * g.v.tiles), block(g.v.R * g.v.LZ);
+  if (xin)
+    hipLaunchKernelGGL((k_post2v<T, CK, false>), grid, block, g.v.lds, s, g, xin, xc, b, xout, poff,
+                       partial, top_begin, (T)omega_a, (T)omega_b);
+  else
+    hipLaunchKernelGGL((k_post2v<T, CK, true>), grid, block, g.v.lds, s, g, xin, xc, b, xout, poff,
+                       partial, top_begin, (T)omega_a, (T)omega_b);
+}
+
+template <typename T>
+bool march_pre2r(const GridArgs& g, const T* dinv, const T* b, T* xout, T* rout, double omega1,
+                 double omega2, bool half, hipStream_t s) {
+  if (!fused_tiles(g) || (half && !pre2r_half_tiles(g))) return false;
+  if (g.rows <= 0) return true;
+  if (g.v.R) {
+    if (sizeof(T) == 4 && g.cache_bf16)
+      launch_pre2v<float, 2>(g, (const float*)dinv, (const float*)b, (float*)xout, (float*)rout,
+                             omega1, omega2, half, s);
+    else
+      launch_pre2v<T, 1>(g, dinv, b, xout, rout, omega1, omega2, half, s);
+    return true;
+  }
+  const int nblk = g.rows * g.t.tiles_per_row;
+#define MLSGD_LAUNCH(TY_, TZ_, CK_, RH_)                                                     \
+  hipLaunchKernelGGL((k_pre2r<T, TY_, TZ_, CK_, RH_>), dim3(nblk), dim3(TY_ * TZ_), 0, s, g, \
+                     dinv, b, xout, rout, (T)omega1, (T)omega2)
+#define MLSGD_LAUNCH2(TY_, TZ_)         \
+  if (b16 && half)                      \
+    MLSGD_LAUNCH(TY_, TZ_, 2, true);    \
+  else if (b16)                         \
+    MLSGD_LAUNCH(TY_, TZ_, 2, false);   \
+  else if (half)                        \
+    MLSGD_LAUNCH(TY_, TZ_, 1, true);    \
+  else                                  \
+    MLSGD_LAUNCH(TY_, TZ_, 1, false)
+  const bool b16 = sizeof(T) == 4 && g.cache_bf16;
+  if (g.t.TZ == 16) {
+    if constexpr (sizeof(T) == 4) {   // 11 and 15 vertices
+      MLSGD_LAUNCH2(16, 16);
+    }
+  } else if (g.t.TY == 8) {
+    MLSGD_LAUNCH2(8, 64);
+  } else {
+    MLSGD_LAUNCH2(16, 64);
+  }
+#undef MLSGD_LAUNCH2
+#undef MLSGD_LAUNCH
+  return true;
+}
+template bool march_pre2r<double>(const GridArgs&, const double*, const double*, double*,
+                                  double*, double, double, bool, hipStream_t);
+template bool march_pre2r<float>(const GridArgs&, const float*, const float*, float*, float*,
+                                 double, double, bool, hipStream_t);
+
 template <typename T>
 bool march_post2(const GridArgs& g, const T* xin, const T* xc, const T* b, T* xout,
                  double omega_a, double omega_b, const int* poff, double* partial, int top_begin,
                  hipStream_t s) {
   if (!fused_tiles(g) || !xc) return false;
   if (g.rows <= 0) return true;
+  if (g.v.R) {
+    if (sizeof(T) == 4 && g.cache_bf16)
+      launch_post2v<float, 2>(g, (const float*)xin, (const float*)xc, (const float*)b,
+                              (float*)xout, omega_a, omega_b, poff, partial, top_begin, s);
+    else
+      launch_post2v<T, 1>(g, xin, xc, b, xout, omega_a, omega_b, poff, partial, top_begin, s);
+    return true;
+  }
   const int nblk = g.rows * g.t.tiles_per_row;
 #define MLSGD_LAUNCH(TY_, TZ_, CK_, XZ_)                                                 \
   hipLaunchKernelGGL((k_post2<T, TY_, TZ_, CK_, XZ_>), dim3(nblk), dim3(TY_ * TZ_), 0, s, g, \
@@ -1403,9 +2013,9 @@ bool march_post2(const GridArgs& g, const T* xin, const T* xc, const T* b, T* xo
     MLSGD_LAUNCH(TY_, TZ_, 1, false)
   const bool b16 = sizeof(T) == 4 && g.cache_bf16;
   if (g.t.TZ == 16) {
-    MLSGD_LAUNCH2(16, 16);
-  } else if (g.t.TZ == 32) {
-    MLSGD_LAUNCH2(8, 32);
+    if constexpr (sizeof(T) == 4) {   // 11 and 15 vertices
+      MLSGD_LAUNCH2(16, 16);
+    }
   } else if (g.t.TY == 8) {
     MLSGD_LAUNCH2(8, 64);
   } else {

@@ -71,6 +71,8 @@ static inline size_t srow(int n) { return (size_t)lay_row(n); }
 struct SizeLvl {
   int n = 0, rows = 0, top_begin = 0;
   Tiling t{};
+  VTile v{};                                        // vector smoothing passes
+  int vslots = 0;                                   // partial slots the last post-smoothing writes
   double *X = nullptr, *B = nullptr, *R = nullptr;  // FP64 multigrid rows (B: Krylov r on top rows)
   double* C = nullptr;                              // FP64 cache of 1/a (null: regenerate)
   float *Xf = nullptr, *Bf = nullptr, *Rf = nullptr;  // FP32 multigrid rows (mixed precision)
@@ -102,7 +104,9 @@ struct Plan {
   int nprob = 0;
   std::vector<int> h_n, h_level;
   std::vector<int64_t> h_sample;
-  std::vector<int> h_poff, h_pcnt;
+  // first partial slot of every problem, the slots its Krylov kernels write, and
+  // those the last post-smoothing pass writes (<r, z>)
+  std::vector<int> h_poff, h_pcnt, h_vcnt;
   std::vector<Group> groups;
   std::vector<SizeLvl> sizes;
   int* d_level = nullptr;
@@ -111,6 +115,7 @@ struct Plan {
   CgScal* d_scal = nullptr;
   int* d_poff = nullptr;
   int* d_pcnt = nullptr;
+  int* d_vcnt = nullptr;
   double* d_partial = nullptr;
   double* d_phi = nullptr;
   double* d_w = nullptr;
@@ -349,6 +354,9 @@ void plan_layout(mlsgd_ctx* c, const std::vector<Block>& blocks, Plan* P, bool s
     }
     s.rows = rows;
     s.t = make_tiling(n, c->tile_y, c->xchunk, split ? rows : 0);
+    if (c->smoother == 2 && (c->mixed ? c->cache32 : c->cache64))
+      s.v = make_vtile(n, c->mixed ? 4 : 8, c->tile_y, c->xchunk, split ? rows : 0);
+    s.vslots = s.v.R && c->post2 && c->nu == 2 ? s.v.tiles : s.t.tiles_per_row;
     s.top_begin = top;
     s.cosT = cos_for(c, n);
     P->sizes.push_back(s);
@@ -369,12 +377,15 @@ void plan_layout(mlsgd_ctx* c, const std::vector<Block>& blocks, Plan* P, bool s
   }
   P->h_pcnt.resize(np);
   P->h_poff.resize(np);
+  P->h_vcnt.resize(np);
   long long off = 0;
   for (const auto& g : P->groups) {
-    const int slots = P->sizes[g.sl].t.tiles_per_row;
+    const SizeLvl& L = P->sizes[g.sl];
+    const int slots = std::max(L.t.tiles_per_row, L.vslots);
     P->max_slots = std::max(P->max_slots, slots);
     for (int q = g.p0; q < g.p0 + g.count; ++q, off += slots) {
-      P->h_pcnt[q] = slots;
+      P->h_pcnt[q] = L.t.tiles_per_row;
+      P->h_vcnt[q] = L.vslots;
       P->h_poff[q] = (int)off;
     }
   }
@@ -419,6 +430,7 @@ size_t plan_carve(mlsgd_ctx* c, Plan* P, char* base) {
   P->d_scal = cv.take<CgScal>(np);
   P->d_poff = cv.take<int>(np);
   P->d_pcnt = cv.take<int>(np);
+  P->d_vcnt = cv.take<int>(np);
   P->d_partial = cv.take<double>((size_t)P->npartial);
   P->d_phi = cv.take<double>(np);
   P->d_w = cv.take<double>(np);
@@ -438,6 +450,8 @@ void plan_init(mlsgd_ctx* c, Plan* P) {
   HIPCHK(hipMemcpyAsync(P->d_poff, P->h_poff.data(), sizeof(int) * P->nprob,
                         hipMemcpyHostToDevice, c->stream));
   HIPCHK(hipMemcpyAsync(P->d_pcnt, P->h_pcnt.data(), sizeof(int) * P->nprob,
+                        hipMemcpyHostToDevice, c->stream));
+  HIPCHK(hipMemcpyAsync(P->d_vcnt, P->h_vcnt.data(), sizeof(int) * P->nprob,
                         hipMemcpyHostToDevice, c->stream));
 }
 
@@ -520,6 +534,7 @@ GridArgs args_size(mlsgd_ctx* c, Plan* P, const SizeLvl& s) {
   g.cache = s.C;
   g.cache_bf16 = 0;
   g.omega1 = 0.0;
+  g.v = s.v;
   return g;
 }
 
@@ -1112,7 +1127,8 @@ void fmg(mlsgd_ctx* c, Plan* P) {
 // is set to 0 for a later phase that counts them.
 void scalar_phase(mlsgd_ctx* c, Plan* P, int phase, bool sums, double rtol, bool count, bool clear,
                   int aux = 0) {
-  cg_scalar(phase, P->d_scal, P->nprob, P->max_slots, P->d_poff, P->d_pcnt,
+  const bool z = phase == PH_RZ0 || phase == PH_RZ;   // sums of the post-smoothing pass
+  cg_scalar(phase, P->d_scal, P->nprob, P->max_slots, P->d_poff, z ? P->d_vcnt : P->d_pcnt,
             sums ? P->d_partial : nullptr, rtol, c->pb.max_iters, count ? c->d_count : nullptr,
             clear ? c->d_count : nullptr, c->stream, aux);
 }
