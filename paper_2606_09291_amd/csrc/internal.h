@@ -157,6 +157,7 @@ bool march_post2(const GridArgs& g, const T* xin, const T* xc, const T* b, T* xo
 // deg-1] (deg <= 8) down and reversed up, exact 3^3 solve, and partials of
 // <b, z> for the problems >= top_begin (partial nullable; one slot each).
 // c9, c5, c3: cached 1/a of the three grids (bfloat16 when cache_bf16).
+// start: instead the full-multigrid start from 3^3 up to 9^3.
 struct VsArgs {
   double om[8];
   int deg;
@@ -166,7 +167,7 @@ constexpr int VS_MAXDEG = 8;
 template <typename T>
 void vcycle_small(int rows, const double* om, int deg, int top_begin, const CgScal* scal,
                   const T* b9, const void* c9, const void* c5, const void* c3, int cache_bf16,
-                  T* xout, const int* poff, double* partial, hipStream_t s);
+                  T* xout, const int* poff, double* partial, bool start, hipStream_t s);
 
 // Whole unpreconditioned CG solves, one workgroup each, of `rows` problems on an
 // n^3 grid (n <= CG_SMALL_MAX) with the cached FP64 1/a: right-hand-side rows

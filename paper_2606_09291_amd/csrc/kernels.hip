@@ -97,6 +97,29 @@ __device__ __forceinline__ double slots_sum(const double* __restrict__ v, int c,
   return sum;
 }
 
+// Wave sum on the DPP path (row shifts, then row broadcasts): lane 63 holds
+// the sum of all 64 lanes, in a fixed order.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ double dpp_add(double v) {
+  union {
+    double d;
+    int i[2];
+  } a, b;
+  a.d = v;
+  b.i[0] = __builtin_amdgcn_update_dpp(0, a.i[0], CTRL, ROWS, 0xf, false);
+  b.i[1] = __builtin_amdgcn_update_dpp(0, a.i[1], CTRL, ROWS, 0xf, false);
+  return v + b.d;
+}
+__device__ __forceinline__ double wave_sum63(double v) {
+  v = dpp_add<0x111, 0xf>(v);   // row_shr:1
+  v = dpp_add<0x112, 0xf>(v);   // row_shr:2
+  v = dpp_add<0x114, 0xf>(v);   // row_shr:4
+  v = dpp_add<0x118, 0xf>(v);   // row_shr:8
+  v = dpp_add<0x142, 0xa>(v);   // row_bcast:15 into rows 1 and 3
+  v = dpp_add<0x143, 0xc>(v);   // row_bcast:31 into rows 2 and 3
+  return v;
+}
+
 template <int NT>
 __device__ __forceinline__ double block_sum(double v, double* sred) {
 #pragma unroll
@@ -2031,207 +2054,306 @@ template bool march_post2<float>(const GridArgs&, const float*, const float*, co
                                  float*, double, double, const int*, double*, int, hipStream_t);
 
 // ---------------------------------------------------------------------------
-// The V-cycle from a 9^3 grid down in one kernel: 9^3 -> 5^3 -> 3^3 and back
-// for every problem of the plan at once, with the level-by-level path's
-// smoothing steps (faces, summation order), transfers and exact 3^3 solve.
-// One workgroup per problem holds all three grids in LDS (right-hand sides,
-// two iterate buffers, reciprocal coefficients): one launch reads b and 1/a
-// and writes z, where the level-by-level cycle makes a dozen launches over
-// these small rows.  The last post-smoothing step forms <b, z> for the
-// problems whose top grid is 9^3 (one partial slot per problem).  As for
-// every grid size, row r of the 9^3, 5^3 and 3^3 rows is problem r, so the
-// workgroup index serves as both.
+// The V-cycle from a 9^3 grid down, 9^3 -> 5^3 -> 3^3 and back, with the
+// level-by-level path's smoothing steps, transfers and exact 3^3 solve, and the
+// full-multigrid start of these three grids.  One wave per problem: a chain of
+// some twenty dependent steps over at most 343 points is bound by the latency of
+// each step, so there is no workgroup barrier and little to recompute.  Lane
+// (y, z) < 7 x 7 holds the x line of its 9^3 column in registers (right-hand
+// side, iterate, faces, reciprocal diagonal), lane i < 27 one 5^3 vertex; LDS
+// passes values to neighbouring lanes only, and lanes of one wave follow each
+// other's LDS operations in order.  As for every grid size, row r of the 9^3, 5^3
+// and 3^3 rows is problem r.  The last post-smoothing step forms <b, z> for the
+// problems whose top grid is 9^3 (one partial slot per problem).
+// Against one 256-thread workgroup per problem with a barrier after every step:
+// 6816 problems 90 -> 60 us (FP64), one problem 11.5 -> 7.8 us; and the start of
+// these grids, some 25 launches of 4 us each level by level, is one of 12 us.
 // ---------------------------------------------------------------------------
-template <typename T, int N>
-struct VsGrid {  // one grid of the small cycle in LDS (dense N^3, boundary zero)
-  static constexpr int M = N - 2, M3 = M * M * M, V = N * N * N;
-  __device__ static int vtx(int i) { return ((1 + i / (M * M)) * N + 1 + (i / M) % M) * N + 1 + i % M; }
-  // one damped Jacobi step x' = x + omega D^-1 (b - A x) (x_zero: x = 0);
-  // returns this thread's share of <b, x'>
-  __device__ static double jac(const T* x, T* xo, const T* b, const T* c, T omega, bool x_zero,
-                               T ih2) {
-    double dot = 0.0;
-    for (int i = threadIdx.x; i < M3; i += blockDim.x) {
-      const int v = vtx(i);
-      const T bc = c[v];
-      const T fxm = face(bc, c[v - N * N]), fxp = face(bc, c[v + N * N]);
-      const T fym = face(bc, c[v - N]), fyp = face(bc, c[v + N]);
-      const T fzm = face(bc, c[v - 1]), fzp = face(bc, c[v + 1]);
-      const T diag = ((fxm + fxp) + (fym + fyp)) + (fzm + fzp);
-      T val;
-      if (x_zero) {
-        val = T(0) + omega * (b[v] - ih2 * (diag * T(0) - T(0))) * drcp(ih2 * diag);
-      } else {
-        const T off = ((fxm * x[v - N * N] + fxp * x[v + N * N]) + (fym * x[v - N] + fyp * x[v + N])) +
-                      (fzm * x[v - 1] + fzp * x[v + 1]);
-        val = x[v] + omega * (b[v] - ih2 * (diag * x[v] - off)) * drcp(ih2 * diag);
-      }
-      xo[v] = val;
-      dot += (double)b[v] * (double)val;
-    }
-    return dot;
-  }
-  __device__ static void resid(const T* x, const T* b, const T* c, T* r, T ih2) {
-    for (int i = threadIdx.x; i < M3; i += blockDim.x) {
-      const int v = vtx(i);
-      const T bc = c[v];
-      const T fxm = face(bc, c[v - N * N]), fxp = face(bc, c[v + N * N]);
-      const T fym = face(bc, c[v - N]), fyp = face(bc, c[v + N]);
-      const T fzm = face(bc, c[v - 1]), fzp = face(bc, c[v + 1]);
-      const T diag = ((fxm + fxp) + (fym + fyp)) + (fzm + fzp);
-      const T off = ((fxm * x[v - N * N] + fxp * x[v + N * N]) + (fym * x[v - N] + fyp * x[v + N])) +
-                    (fzm * x[v - 1] + fzp * x[v + 1]);
-      r[v] = b[v] - ih2 * (diag * x[v] - off);
-    }
-  }
-  // full weighting of the fine residual r onto this (coarse) grid's b
-  __device__ static void restrict_from(const T* r, T* bc) {
-    constexpr int NF = 2 * (N - 1) + 1;
-    for (int i = threadIdx.x; i < M3; i += blockDim.x) {
-      const int jx = 1 + i / (M * M), jy = 1 + (i / M) % M, jz = 1 + i % M;
-      T acc = T(0);
-#pragma unroll
-      for (int dx = -1; dx <= 1; ++dx) {
-        const T wx = dx == 0 ? T(0.5) : T(0.25);
-        T ay = T(0);
-#pragma unroll
-        for (int dy = -1; dy <= 1; ++dy) {
-          const T wy = dy == 0 ? T(0.5) : T(0.25);
-          const T* p = r + ((2 * jx + dx) * NF + (2 * jy + dy)) * NF + 2 * jz;
-          ay += wy * (T(0.25) * p[-1] + T(0.5) * p[0] + T(0.25) * p[1]);
-        }
-        acc += wx * ay;
-      }
-      bc[vtx(i)] = acc;
-    }
-  }
-  // x (this fine grid) += trilinear prolongation of the coarse xc
-  __device__ static void prolong_add(const T* xc, T* x) {
-    constexpr int NC = (N - 1) / 2 + 1;
-    for (int i = threadIdx.x; i < M3; i += blockDim.x) {
-      const int v = vtx(i);
-      const int ix = 1 + i / (M * M), iy = 1 + (i / M) % M, iz = 1 + i % M;
-      x[v] += prolong_val<T>(NC, xc, ix, iy, iz);
-    }
-  }
+__device__ __forceinline__ void wave_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+constexpr int VS_WAVES = 4;   // problems per workgroup
+
+template <typename T>
+struct VsLds {          // one wave's LDS
+  T v9[9 * 9 * 9];      // values (or 1/a) of the 9^3 vertices, boundary zero
+  T v5[5 * 5 * 5];      // the same for 5^3
 };
 
 template <typename T, int CK>
-__global__ void __launch_bounds__(256)
-    k_vsmall(VsArgs va, const CgScal* __restrict__ scal, const T* __restrict__ b9,
-             const void* __restrict__ c9, const void* __restrict__ c5,
-             const void* __restrict__ c3, T* __restrict__ xout, const int* __restrict__ poff,
-             double* __restrict__ partial) {
+struct VsWave {
   using CR = typename std::conditional<CK == 2, uint16_t, T>::type;
-  using G9 = VsGrid<T, 9>;
-  using G5 = VsGrid<T, 5>;
-  using G3 = VsGrid<T, 3>;
-  __shared__ T sb9[729], sx9[2][729], sc9[729];
-  __shared__ T sb5[125], sx5[2][125], sc5[125];
-  __shared__ T sb3[27], sx3[27], sc3[27];
-  __shared__ double sred[4];
-  const int prob = blockIdx.x;
-  if (scal && !scal[prob].active) return;  // uniform per workgroup
-  const int tid = threadIdx.x;
-  auto cvt = [&](CR v) -> T {
+  VsLds<T>& s;
+  int lane, o9, o5;            // LDS slot of plane x = 1 of the 9^3 column; of the 5^3 vertex
+  bool on9, on5;
+  T b[7], x[7], di[7], fx[8], fym[7], fyp[7], fzm[7], fzp[7];   // 9^3 column
+  T b5, x5, di5, f5[6];                                         // 5^3 vertex (x-, x+, y-, y+, z-, z+)
+  T di3;                                                        // 3^3 vertex (every lane)
+  __device__ static T cvt(CR v) {
     if constexpr (CK == 2)
       return (T)from_bf16(v);
     else
       return v;
-  };
-  const CR* C9 = (const CR*)c9 + (size_t)prob * 729;
-  const CR* C5 = (const CR*)c5 + (size_t)prob * 125;
-  const CR* C3 = (const CR*)c3 + (size_t)prob * 27;
-  for (int v = tid; v < 729; v += 256) {
-    sb9[v] = b9[(size_t)prob * 729 + v];
-    sc9[v] = cvt(C9[v]);
-    sx9[0][v] = T(0);
-    sx9[1][v] = T(0);
   }
-  for (int v = tid; v < 125; v += 256) {
-    sc5[v] = cvt(C5[v]);
-    sb5[v] = T(0);
-    sx5[0][v] = T(0);
-    sx5[1][v] = T(0);
+  __device__ VsWave(VsLds<T>& lds, int ln) : s(lds), lane(ln) {
+    const int ly = lane >> 3, lz = lane & 7;
+    on9 = ly < 7 && lz < 7;
+    o9 = 81 + (on9 ? (1 + ly) * 9 + 1 + lz : 10);
+    on5 = lane < 27;
+    const int i = on5 ? lane : 0;
+    o5 = ((1 + i / 9) * 5 + 1 + (i / 3) % 3) * 5 + 1 + i % 3;
   }
-  if (tid < 27) {
-    sc3[tid] = cvt(C3[tid]);
-    sb3[tid] = T(0);
-    sx3[tid] = T(0);
+  // faces and reciprocal diagonals of the three grids from their cached 1/a,
+  // then zero value arrays
+  __device__ void coefficients(const CR* c9, const CR* c5, const CR* c3) {
+    for (int v = lane; v < 729; v += 64) s.v9[v] = cvt(c9[v]);
+    for (int v = lane; v < 125; v += 64) s.v5[v] = cvt(c5[v]);
+    T f3 = T(0);
+    {
+      const T bc = cvt(c3[13]);
+      f3 = ((face(bc, cvt(c3[4])) + face(bc, cvt(c3[22]))) +
+            (face(bc, cvt(c3[10])) + face(bc, cvt(c3[16])))) +
+           (face(bc, cvt(c3[12])) + face(bc, cvt(c3[14])));
+    }
+    di3 = drcp(T(4) * f3);
+    wave_sync();
+#pragma unroll
+    for (int k = 0; k < 8; ++k) fx[k] = face(s.v9[o9 + (k - 1) * 81], s.v9[o9 + k * 81]);
+#pragma unroll
+    for (int k = 0; k < 7; ++k) {
+      const int o = o9 + k * 81;
+      const T bc = s.v9[o];
+      fym[k] = face(bc, s.v9[o - 9]);
+      fyp[k] = face(bc, s.v9[o + 9]);
+      fzm[k] = face(bc, s.v9[o - 1]);
+      fzp[k] = face(bc, s.v9[o + 1]);
+      di[k] = drcp(T(64) * diag(k));
+    }
+    {
+      const T bc = s.v5[o5];
+      f5[0] = face(bc, s.v5[o5 - 25]);
+      f5[1] = face(bc, s.v5[o5 + 25]);
+      f5[2] = face(bc, s.v5[o5 - 5]);
+      f5[3] = face(bc, s.v5[o5 + 5]);
+      f5[4] = face(bc, s.v5[o5 - 1]);
+      f5[5] = face(bc, s.v5[o5 + 1]);
+      di5 = drcp(T(16) * diag5());
+    }
+    wave_sync();
+    for (int v = lane; v < 729; v += 64) s.v9[v] = T(0);
+    for (int v = lane; v < 125; v += 64) s.v5[v] = T(0);
+    wave_sync();
   }
-  __syncthreads();
-  const T ih9 = T(64), ih5 = T(16), ih3 = T(4);
-  const int deg = va.deg;
-  // pre-smoothing from zero and residual on 9^3, restriction to 5^3
-  int c9c = 0;
-  for (int j = 0; j < deg; ++j) {
-    G9::jac(sx9[c9c], sx9[c9c ^ 1], sb9, sc9, (T)va.om[j], j == 0, ih9);
-    c9c ^= 1;
-    __syncthreads();
+  __device__ T diag(int k) const { return ((fx[k] + fx[k + 1]) + (fym[k] + fyp[k])) + (fzm[k] + fzp[k]); }
+  __device__ T diag5() const { return ((f5[0] + f5[1]) + (f5[2] + f5[3])) + (f5[4] + f5[5]); }
+  // publish the column's (vertex's) values; sums of faces times neighbours
+  __device__ void put9(const T (&v)[7]) {
+    wave_sync();
+    if (on9) {
+#pragma unroll
+      for (int k = 0; k < 7; ++k) s.v9[o9 + k * 81] = v[k];
+    }
+    wave_sync();
   }
-  G9::resid(sx9[c9c], sb9, sc9, sx9[c9c ^ 1], ih9);
-  __syncthreads();
-  G5::restrict_from(sx9[c9c ^ 1], sb5);
-  __syncthreads();
-  // the same on 5^3, restriction to 3^3
-  int c5c = 0;
-  for (int j = 0; j < deg; ++j) {
-    G5::jac(sx5[c5c], sx5[c5c ^ 1], sb5, sc5, (T)va.om[j], j == 0, ih5);
-    c5c ^= 1;
-    __syncthreads();
+  __device__ void put5(T v) {
+    wave_sync();
+    if (on5) s.v5[o5] = v;
+    wave_sync();
   }
-  G5::resid(sx5[c5c], sb5, sc5, sx5[c5c ^ 1], ih5);
-  __syncthreads();
-  G3::restrict_from(sx5[c5c ^ 1], sb3);
-  __syncthreads();
-  // exact solve of the single 3^3 unknown
-  G3::jac(sx3, sx3, sb3, sc3, T(1), true, ih3);
-  __syncthreads();
-  // up: correction and post-smoothing on 5^3, then on 9^3
-  G5::prolong_add(sx3, sx5[c5c]);
-  __syncthreads();
-  for (int j = 0; j < deg; ++j) {
-    G5::jac(sx5[c5c], sx5[c5c ^ 1], sb5, sc5, (T)va.om[deg - 1 - j], false, ih5);
-    c5c ^= 1;
-    __syncthreads();
+  __device__ T off(int k) const {
+    const int o = o9 + k * 81;
+    const T xm = k > 0 ? x[k > 0 ? k - 1 : 0] : T(0), xp = k < 6 ? x[k < 6 ? k + 1 : 0] : T(0);
+    return ((fx[k] * xm + fx[k + 1] * xp) + (fym[k] * s.v9[o - 9] + fyp[k] * s.v9[o + 9])) +
+           (fzm[k] * s.v9[o - 1] + fzp[k] * s.v9[o + 1]);
   }
-  G9::prolong_add(sx5[c5c], sx9[c9c]);
-  __syncthreads();
-  double dot = 0.0;
-  for (int j = 0; j < deg; ++j) {
-    dot = G9::jac(sx9[c9c], sx9[c9c ^ 1], sb9, sc9, (T)va.om[deg - 1 - j], false, ih9);
-    c9c ^= 1;
-    __syncthreads();
+  __device__ T off5() const {
+    return ((f5[0] * s.v5[o5 - 25] + f5[1] * s.v5[o5 + 25]) +
+            (f5[2] * s.v5[o5 - 5] + f5[3] * s.v5[o5 + 5])) +
+           (f5[4] * s.v5[o5 - 1] + f5[5] * s.v5[o5 + 1]);
   }
-  for (int v = tid; v < 729; v += 256) xout[(size_t)prob * 729 + v] = sx9[c9c][v];
+  // x <- x + omega D^-1 (b - A x)
+  __device__ void jac9(T om) {
+    put9(x);
+    T y[7];
+#pragma unroll
+    for (int k = 0; k < 7; ++k) y[k] = x[k] + om * ((b[k] + T(64) * off(k)) * di[k] - x[k]);
+#pragma unroll
+    for (int k = 0; k < 7; ++k) x[k] = y[k];
+  }
+  __device__ void jac5(T om) {
+    put5(x5);
+    x5 = x5 + om * ((b5 + T(16) * off5()) * di5 - x5);
+  }
+  // right-hand side of 5^3: full weighting of the 9^3 field w (zero boundary)
+  __device__ void restrict9(const T (&w)[7]) {
+    put9(w);
+    const int i = on5 ? lane : 0;
+    const int c = ((2 * (1 + i / 9)) * 9 + 2 * (1 + (i / 3) % 3)) * 9 + 2 * (1 + i % 3);
+    T acc = T(0);
+#pragma unroll
+    for (int dx = -1; dx <= 1; ++dx) {
+      T ay = T(0);
+#pragma unroll
+      for (int dy = -1; dy <= 1; ++dy) {
+        const T* p = &s.v9[c + dx * 81 + dy * 9];
+        ay += (dy == 0 ? T(0.5) : T(0.25)) * (T(0.25) * p[-1] + T(0.5) * p[0] + T(0.25) * p[1]);
+      }
+      acc += (dx == 0 ? T(0.5) : T(0.25)) * ay;
+    }
+    b5 = acc;
+  }
+  // the exact 3^3 solution for the full weighting of the 5^3 field w (every lane)
+  __device__ T solve3(T w) {
+    put5(w);
+    T acc = T(0);
+#pragma unroll
+    for (int dx = -1; dx <= 1; ++dx) {
+      T ay = T(0);
+#pragma unroll
+      for (int dy = -1; dy <= 1; ++dy) {
+        const T* p = &s.v5[62 + dx * 25 + dy * 5];
+        ay += (dy == 0 ? T(0.5) : T(0.25)) * (T(0.25) * p[-1] + T(0.5) * p[0] + T(0.25) * p[1]);
+      }
+      acc += (dx == 0 ? T(0.5) : T(0.25)) * ay;
+    }
+    return acc * di3;
+  }
+  // trilinear prolongation of the 3^3 value to the lane's 5^3 vertex
+  __device__ T prolong3(T x3) const {
+    const int i = on5 ? lane : 0;
+    const T wx = i / 9 == 1 ? T(1) : T(0.5), wy = (i / 3) % 3 == 1 ? T(1) : T(0.5),
+            wz = i % 3 == 1 ? T(1) : T(0.5);
+    return (wx * wy * wz) * x3;
+  }
+  // prolongation of the 5^3 iterate to the column: added to x, or (set) as x
+  __device__ void prolong5(bool set) {
+    put5(x5);
+    const int iy = 1 + (on9 ? lane >> 3 : 0), iz = 1 + (on9 ? lane & 7 : 0);
+    const int dy = (iy & 1) ? 5 : 0, dz = iz & 1;
+    const T* p = &s.v5[(iy >> 1) * 5 + (iz >> 1)];
+    T w[5];
+#pragma unroll
+    for (int j = 0; j < 5; ++j)
+      w[j] = T(0.25) * ((p[j * 25] + p[j * 25 + dz]) + (p[j * 25 + dy] + p[j * 25 + dy + dz]));
+#pragma unroll
+    for (int k = 0; k < 7; ++k) {
+      const T v = (k & 1) ? w[(k + 1) / 2] : T(0.5) * (w[k / 2] + w[k / 2 + 1]);
+      x[k] = set ? v : x[k] + v;
+    }
+  }
+  __device__ void resid9(T (&r)[7]) {
+    put9(x);
+#pragma unroll
+    for (int k = 0; k < 7; ++k) r[k] = b[k] - T(64) * (diag(k) * x[k] - off(k));
+  }
+  // the rest of a 5^3 cycle after its pre-smoothing
+  __device__ void coarse5(const VsArgs& va) {
+    put5(x5);
+    const T r5 = b5 - T(16) * (diag5() * x5 - off5());
+    x5 += prolong3(solve3(r5));
+    for (int j = va.deg - 1; j >= 0; --j) jac5((T)va.om[j]);
+  }
+  // coarse-grid correction and post-smoothing of a 9^3 cycle after its
+  // pre-smoothing: residual, a 5^3 cycle from zero, prolongation
+  __device__ void coarse9(const VsArgs& va) {
+    T r[7];
+    resid9(r);
+    restrict9(r);
+    x5 = (T)va.om[0] * (b5 * di5);
+    for (int j = 1; j < va.deg; ++j) jac5((T)va.om[j]);
+    coarse5(va);
+    prolong5(false);
+    for (int j = va.deg - 1; j >= 0; --j) jac9((T)va.om[j]);
+  }
+};
+
+// START: the full-multigrid start of the three grids instead of a cycle from zero
+template <typename T, int CK, bool START>
+__global__ void __launch_bounds__(64 * VS_WAVES)
+    k_vsmall(VsArgs va, int rows, const CgScal* __restrict__ scal, const T* __restrict__ b9,
+             const void* __restrict__ c9, const void* __restrict__ c5,
+             const void* __restrict__ c3, T* __restrict__ xout, const int* __restrict__ poff,
+             double* __restrict__ partial) {
+  using CR = typename VsWave<T, CK>::CR;
+  __shared__ VsLds<T> lds[VS_WAVES];
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int prob = blockIdx.x * VS_WAVES + wave;
+  if (prob >= rows || (scal && !scal[prob].active)) return;  // uniform per wave, no barriers
+  VsWave<T, CK> w(lds[wave], lane);
+  const T* brow = b9 + (size_t)prob * 729;
+#pragma unroll
+  for (int k = 0; k < 7; ++k) {
+    const T v = brow[w.o9 + k * 81];
+    w.b[k] = w.on9 ? v : T(0);
+  }
+  w.coefficients((const CR*)c9 + (size_t)prob * 729, (const CR*)c5 + (size_t)prob * 125,
+                 (const CR*)c3 + (size_t)prob * 27);
+  if constexpr (START) {
+    // b on 5^3 and 3^3, the exact 3^3 solution, then one cycle a grid from the
+    // prolonged solution of the grid below
+    w.restrict9(w.b);
+    w.x5 = w.prolong3(w.solve3(w.b5));
+    for (int j = 0; j < va.deg; ++j) w.jac5((T)va.om[j]);
+    w.coarse5(va);
+    w.prolong5(true);
+    for (int j = 0; j < va.deg; ++j) w.jac9((T)va.om[j]);
+  } else {
+#pragma unroll
+    for (int k = 0; k < 7; ++k) w.x[k] = (T)va.om[0] * (w.b[k] * w.di[k]);
+    for (int j = 1; j < va.deg; ++j) w.jac9((T)va.om[j]);
+  }
+  w.coarse9(va);
+  T* xrow = xout + (size_t)prob * 729;
+  if (w.on9) {
+#pragma unroll
+    for (int k = 0; k < 7; ++k) xrow[w.o9 + k * 81] = w.x[k];
+  }
   if (partial != nullptr && prob >= va.top_begin) {
-    const double s = block_sum<256>(dot, sred);
-    if (tid == 0) partial[poff[prob]] = s;
+    double dot = 0.0;
+    if (w.on9) {
+#pragma unroll
+      for (int k = 0; k < 7; ++k) dot += (double)w.b[k] * (double)w.x[k];
+    }
+    dot = wave_sum63(dot);
+    if (lane == 63) partial[poff[prob]] = dot;
   }
 }
 
 template <typename T>
 void vcycle_small(int rows, const double* om, int deg, int top_begin, const CgScal* scal,
                   const T* b9, const void* c9, const void* c5, const void* c3, int cache_bf16,
-                  T* xout, const int* poff, double* partial, hipStream_t s) {
+                  T* xout, const int* poff, double* partial, bool start, hipStream_t s) {
   if (rows <= 0) return;
   VsArgs va{};
   for (int j = 0; j < deg && j < VS_MAXDEG; ++j) va.om[j] = om[j];
   va.deg = deg;
   va.top_begin = top_begin;
-  if (sizeof(T) == 4 && cache_bf16)
-    hipLaunchKernelGGL((k_vsmall<T, 2>), dim3(rows), dim3(256), 0, s, va, scal, b9, c9, c5, c3,
-                       xout, poff, partial);
-  else
-    hipLaunchKernelGGL((k_vsmall<T, 1>), dim3(rows), dim3(256), 0, s, va, scal, b9, c9, c5, c3,
-                       xout, poff, partial);
+#define MLSGD_LAUNCH(CK_, START_)                                                             \
+  hipLaunchKernelGGL((k_vsmall<T, CK_, START_>), dim3(cdiv(rows, VS_WAVES)), dim3(64 * VS_WAVES), \
+                     0, s, va, rows, scal, b9, c9, c5, c3, xout, poff, partial)
+  if (sizeof(T) == 4 && cache_bf16) {
+    if constexpr (sizeof(T) == 4) {
+      if (start)
+        MLSGD_LAUNCH(2, true);
+      else
+        MLSGD_LAUNCH(2, false);
+    }
+  } else if (start) {
+    MLSGD_LAUNCH(1, true);
+  } else {
+    MLSGD_LAUNCH(1, false);
+  }
+#undef MLSGD_LAUNCH
 }
 template void vcycle_small<double>(int, const double*, int, int, const CgScal*, const double*,
                                    const void*, const void*, const void*, int, double*, const int*,
-                                   double*, hipStream_t);
+                                   double*, bool, hipStream_t);
 template void vcycle_small<float>(int, const double*, int, int, const CgScal*, const float*,
                                   const void*, const void*, const void*, int, float*, const int*,
-                                  double*, hipStream_t);
+                                  double*, bool, hipStream_t);
 
 // ---------------------------------------------------------------------------
 // Unpreconditioned CG on small grids (at most 17^3), a whole solve per
@@ -2246,29 +2368,6 @@ template void vcycle_small<float>(int, const double*, int, int, const CgScal*, c
 // (the dots' summation order differs).  64 solves of 17^3 to 1e-12 (about 100
 // iterations): 3.3 ms level by level, 0.19 ms here.
 // ---------------------------------------------------------------------------
-// Wave sum on the DPP path (row shifts, then row broadcasts): lane 63 holds
-// the sum of all 64 lanes, in a fixed order.
-template <int CTRL, int ROWS>
-__device__ __forceinline__ double dpp_add(double v) {
-  union {
-    double d;
-    int i[2];
-  } a, b;
-  a.d = v;
-  b.i[0] = __builtin_amdgcn_update_dpp(0, a.i[0], CTRL, ROWS, 0xf, false);
-  b.i[1] = __builtin_amdgcn_update_dpp(0, a.i[1], CTRL, ROWS, 0xf, false);
-  return v + b.d;
-}
-__device__ __forceinline__ double wave_sum63(double v) {
-  v = dpp_add<0x111, 0xf>(v);   // row_shr:1
-  v = dpp_add<0x112, 0xf>(v);   // row_shr:2
-  v = dpp_add<0x114, 0xf>(v);   // row_shr:4
-  v = dpp_add<0x118, 0xf>(v);   // row_shr:8
-  v = dpp_add<0x142, 0xa>(v);   // row_bcast:15 into rows 1 and 3
-  v = dpp_add<0x143, 0xc>(v);   // row_bcast:31 into rows 2 and 3
-  return v;
-}
-
 // CY x CY columns (n - 2 <= CY), NS segments of XS x planes (n - 2 <= NS XS)
 template <int CY, int NS, int XS>
 __global__ void __launch_bounds__(CY* CY* NS)

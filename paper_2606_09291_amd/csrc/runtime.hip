@@ -752,6 +752,23 @@ const double* dinv_of<double>(const SizeLvl& L) { return L.Di; }
 template <>
 const float* dinv_of<float>(const SizeLvl& L) { return L.Dif; }
 
+// The one-kernel cycle from 9^3 down applies where the hierarchy ends 9^3, 5^3,
+// 3^3 with cached coefficients and every problem on 5^3 and 3^3 comes down from
+// 9^3 (none has its top grid there); it writes a problem's <r, z> partial into
+// its one 9^3 slot.
+template <typename T>
+bool small_cycle(mlsgd_ctx* c, Plan* P) {
+  const int S = (int)P->sizes.size();
+  if (!c->vsmall || S < 3 || P->ainv || c->nu > VS_MAXDEG) return false;
+  const SizeLvl &L9 = P->sizes[S - 3], &L5 = P->sizes[S - 2], &L3 = P->sizes[S - 1];
+  if (L9.n != 9 || L5.n != 5 || L3.n != 3 || L5.top_begin != L5.rows ||
+      L3.top_begin != L3.rows || L5.rows != L9.rows || L9.t.tiles_per_row != 1)
+    return false;
+  for (const SizeLvl* L : {&L9, &L5, &L3})
+    if (!(sizeof(T) == 8 ? args_size(c, P, *L) : args_size32(c, P, *L)).cache) return false;
+  return true;
+}
+
 //
 // k0, rlim, xinit serve the full-multigrid start: the cycle then begins on
 // grid size k0, covers rows 0 .. rlim-1 of every size (the problems whose top
@@ -767,21 +784,9 @@ void vcycle_cheb(mlsgd_ctx* c, Plan* P, int k0 = 0, int rlim = INT_MAX, bool xin
     g.rows = std::min(g.rows, rlim);
     return g;
   };
-  // the levels from 9^3 down run as one LDS-resident kernel where the
-  // hierarchy ends 9^3, 5^3, 3^3 with cached coefficients and every problem
-  // on 5^3 and 3^3 comes down from 9^3 (none has its top grid there)
+  // the levels from 9^3 down run as one kernel where small_cycle allows
   int ks = S;
-  if (c->vsmall && S >= 3 && S - 3 >= k0 && !(xinit && S - 3 == k0) && !P->ainv &&
-      P->sizes[S - 3].n == 9 && P->sizes[S - 2].n == 5 &&
-      P->sizes[S - 1].n == 3 && (int)om.size() <= VS_MAXDEG &&
-      P->sizes[S - 2].top_begin == P->sizes[S - 2].rows &&
-      P->sizes[S - 1].top_begin == P->sizes[S - 1].rows &&
-      P->sizes[S - 2].rows == P->sizes[S - 3].rows) {
-    const GridArgs g9 = args(P->sizes[S - 3]), g5 = args(P->sizes[S - 2]),
-                   g3 = args(P->sizes[S - 1]);
-    // the kernel writes a problem's <r, z> partial into its one 9^3 slot
-    if (g9.cache && g5.cache && g3.cache && g9.t.tiles_per_row == 1) ks = S - 3;
-  }
+  if (small_cycle<T>(c, P) && S - 3 >= k0 && !(xinit && S - 3 == k0)) ks = S - 3;
   for (int k = k0; k < S; ++k) {
     SizeLvl& L = P->sizes[k];
     MgView<T> v = mg_view<T>(L);
@@ -790,7 +795,7 @@ void vcycle_cheb(mlsgd_ctx* c, Plan* P, int k0 = 0, int rlim = INT_MAX, bool xin
     if (k == ks) {
       const GridArgs g5 = args(P->sizes[k + 1]), g3 = args(P->sizes[k + 2]);
       vcycle_small<T>(g.rows, om.data(), deg, L.top_begin, P->d_scal, v.B, g.cache, g5.cache,
-                      g3.cache, g.cache_bf16, A[0], P->d_poff, P->d_partial, c->stream);
+                      g3.cache, g.cache_bf16, A[0], P->d_poff, P->d_partial, false, c->stream);
       L.cur = 0;
       break;
     }
@@ -1084,29 +1089,41 @@ void fmg_start(mlsgd_ctx* c, Plan* P) {
              L.Bf + (size_t)gr.p0 * srow(gr.n), s);
     }
   }
-  for (int k = 0; k + 1 < S; ++k) {
+  // kb: the largest grid whose start is ready
+  const bool small = small_cycle<T>(c, P);
+  const int kb = small ? S - 3 : S - 1;
+  for (int k = 0; k < kb; ++k) {
     SizeLvl& L = P->sizes[k];
     restrict_rows<T>(L.n, L.rows, 0, nullptr, mg_view<T>(L).B, mg_view<T>(P->sizes[k + 1]).B, s);
   }
-  {
-    SizeLvl& L = P->sizes[S - 1];
-    GridArgs g = sizeof(T) == 8 ? args_size(c, P, L) : args_size32(c, P, L);
-    march_jac<T>(g, nullptr, nullptr, mg_view<T>(L).B, mg_view<T>(L).X, 1, 1.0, nullptr, nullptr,
-                 0, s);
-    L.cur = 0;
-    for (auto& gr : P->groups)
-      if (gr.sl == S - 1)
-        copy_active_rows<T>(gr.n, gr.count, gr.p0, P->d_scal,
-                            mg_view<T>(L).X + (size_t)gr.p0 * srow(gr.n), gr.x, s);
-  }
-  for (int k = S - 2; k >= 0; --k) {
+  auto start = [&](int k) {   // a problem's result on its top grid becomes x0
     SizeLvl& L = P->sizes[k];
-    vcycle_cheb<T>(c, P, k, L.rows, true);
     const T* xk = L.cur ? mg_view<T>(L).R : mg_view<T>(L).X;
     for (auto& gr : P->groups)
       if (gr.sl == k)
         copy_active_rows<T>(gr.n, gr.count, gr.p0, P->d_scal, xk + (size_t)gr.p0 * srow(gr.n),
                             gr.x, s);
+  };
+  auto args = [&](SizeLvl& L) {
+    return sizeof(T) == 8 ? args_size(c, P, L) : args_size32(c, P, L);
+  };
+  {
+    SizeLvl& L = P->sizes[kb];
+    if (small) {   // 3^3, 5^3 and 9^3 in one kernel
+      const std::vector<double> om = cheb_omegas(c->nu, c->cheb_lo);
+      const GridArgs g9 = args(L), g5 = args(P->sizes[S - 2]), g3 = args(P->sizes[S - 1]);
+      vcycle_small<T>(L.rows, om.data(), c->nu, 0, P->d_scal, mg_view<T>(L).B, g9.cache, g5.cache,
+                      g3.cache, g9.cache_bf16, mg_view<T>(L).X, nullptr, nullptr, true, s);
+    } else {
+      march_jac<T>(args(L), nullptr, nullptr, mg_view<T>(L).B, mg_view<T>(L).X, 1, 1.0, nullptr,
+                   nullptr, 0, s);
+    }
+    L.cur = 0;
+    start(kb);
+  }
+  for (int k = kb - 1; k >= 0; --k) {
+    vcycle_cheb<T>(c, P, k, P->sizes[k].rows, true);
+    start(k);
   }
   for (auto& gr : P->groups) {
     GridArgs g = args_group(c, P, gr, false);
