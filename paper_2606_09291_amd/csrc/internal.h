@@ -113,11 +113,24 @@ template <typename T>
 void rb_sweep(const GridArgs& g, const T* xin, const T* xc, const T* b, T* xout,
               int first_color, int x_zero, const int* poff, double* partial, int top_begin,
               double omega, hipStream_t s);
-void coef_cache(int n, int rows, const double* coef, int K, const double* cosT, double* out64,
-                float* out32, uint16_t* out16, hipStream_t s);
-// reciprocal diagonal 1 / (h^-2 sum_f a_f) of every row from the cached 1/a
-template <typename T>
-void dinv_rows(int n, int rows, const void* cache, int cache_bf16, T* dinv, hipStream_t s);
+// The per-estimate fields of every grid size: 1/a regenerated from the KL
+// coefficients into the caches that are set (null: none), and from them the
+// reciprocal diagonals 1 / (h^-2 sum_f a_f) of the V-cycle's type where set.
+struct FieldLvl {
+  int n, rows;
+  const double* cosT;
+  double* c64;      // FP64 cache of 1/a
+  float* c32;       // FP32 cache
+  uint16_t* c16;    // bfloat16 cache
+  void* dinv;       // reciprocal diagonal, double from c64 alone, else float
+  int xch, nxc, cblk0, dper, dblk0;   // launch layout (set by field_caches)
+};
+constexpr int MAX_SIZES = 12;
+struct FieldTable {
+  FieldLvl lv[MAX_SIZES];
+  int count;
+};
+void field_caches(FieldTable& ft, const double* coef, int K, hipStream_t s);
 // two Jacobi steps from x = 0 in one pass: x2 = J(omega2) J(omega1) 0 (the
 // first step x1 = omega1 b / D is formed on the fly from b and 1/D)
 template <typename T>

@@ -12,6 +12,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <cstdio>
 #include <cstdlib>
@@ -2531,54 +2532,48 @@ void cg_small(int n, int rows, int row0, CgScal* scal, const double* cache, cons
 }
 
 // Reciprocal diagonal drcp(h^-2 ((fxm + fxp) + (fym + fyp)) + (fzm + fzp)) of
-// every interior vertex, with the faces and the summation order of k_march,
-// so the first smoothing step formed from it equals the one k_march forms.
+// every interior vertex of every row of every grid size, with the faces and the
+// summation order of k_march.  One launch for all sizes, as for the coefficient
+// caches it reads (k_coef_cache); a workgroup takes DINV_CHUNK elements of a row,
+// with 32-bit coordinates.
+constexpr int DINV_CHUNK = 256 * 8;
+
 template <typename T, int CK>
-__global__ void k_dinv(int n, long long total, const void* __restrict__ cache, T ih2,
-                       T* __restrict__ dinv) {
-  const long long per = lay_row(n);
-  const int LP = lay_pitch(n), LO = lay_off(n);
-  const T* c = (const T*)cache;
-  const uint16_t* c16 = (const uint16_t*)cache;
-  auto bval = [&](long long e) -> T {
+__global__ void __launch_bounds__(256) k_dinv(FieldTable ft) {
+  int k = 0;
+  while (k + 1 < ft.count && blockIdx.x >= (unsigned)ft.lv[k + 1].dblk0) ++k;   // uniform
+  const FieldLvl& L = ft.lv[k];
+  const int n = L.n, LP = lay_pitch(n), LO = lay_off(n);
+  const uint32_t per = (uint32_t)lay_row(n);
+  const int blk = (int)blockIdx.x - L.dblk0;
+  const int row = blk / L.dper;
+  const uint32_t e0 = (uint32_t)(blk - row * L.dper) * DINV_CHUNK;
+  const T* c = (const T*)(sizeof(T) == 8 ? (const void*)L.c64 : (const void*)L.c32) + (size_t)row * per;
+  const uint16_t* c16 = L.c16 + (size_t)row * per;
+  T* __restrict__ dinv = (T*)L.dinv + (size_t)row * per;
+  const T ih2 = (T)((double)(n - 1) * (double)(n - 1));
+  auto bval = [&](uint32_t e) -> T {
     if constexpr (CK == 2)
       return (T)from_bf16(c16[e]);
     else
       return c[e];
   };
-  for (long long e = (long long)blockIdx.x * blockDim.x + threadIdx.x; e < total;
-       e += (long long)gridDim.x * blockDim.x) {
-    const long long v = e % per;
-    const int ix = (int)(v / ((long long)n * LP)), iy = (int)((v / LP) % n),
-              iz = (int)(v % LP) - LO;
-    if (ix < 1 || iy < 1 || iz < 1 || ix > n - 2 || iy > n - 2 || iz > n - 2) {
-      dinv[e] = T(0);
-      continue;
+  const uint32_t sx = (uint32_t)n * LP, sy = LP;
+#pragma unroll 2
+  for (uint32_t e = e0 + threadIdx.x; e < min(e0 + DINV_CHUNK, per); e += 256) {
+    const uint32_t ix = e / sx, r = e - ix * sx, iy = r / sy;
+    const int iz = (int)(r - iy * sy) - LO;
+    T d = T(0);
+    if (ix >= 1 && iy >= 1 && iz >= 1 && (int)ix <= n - 2 && (int)iy <= n - 2 && iz <= n - 2) {
+      const T bc = bval(e);
+      const T fxm = face(bval(e - sx), bc), fxp = face(bc, bval(e + sx));
+      const T fym = face(bc, bval(e - sy)), fyp = face(bc, bval(e + sy));
+      const T fzm = face(bc, bval(e - 1)), fzp = face(bc, bval(e + 1));
+      d = drcp(ih2 * (((fxm + fxp) + (fym + fyp)) + (fzm + fzp)));
     }
-    const long long sx = (long long)n * LP, sy = LP;
-    const T bc = bval(e);
-    const T fxm = face(bval(e - sx), bc), fxp = face(bc, bval(e + sx));
-    const T fym = face(bc, bval(e - sy)), fyp = face(bc, bval(e + sy));
-    const T fzm = face(bc, bval(e - 1)), fzp = face(bc, bval(e + 1));
-    const T diag = ((fxm + fxp) + (fym + fyp)) + (fzm + fzp);
-    dinv[e] = drcp(ih2 * diag);
+    dinv[e] = d;
   }
 }
-
-template <typename T>
-void dinv_rows(int n, int rows, const void* cache, int cache_bf16, T* dinv, hipStream_t s) {
-  const long long total = (long long)rows * lay_row(n);
-  if (total <= 0 || !cache || !dinv) return;
-  const T ih2 = (T)((double)(n - 1) * (double)(n - 1));
-  if (cache_bf16)
-    hipLaunchKernelGGL((k_dinv<T, 2>), dim3(grid_for(total, 256)), dim3(256), 0, s, n, total,
-                       cache, ih2, dinv);
-  else
-    hipLaunchKernelGGL((k_dinv<T, 1>), dim3(grid_for(total, 256)), dim3(256), 0, s, n, total,
-                       cache, ih2, dinv);
-}
-template void dinv_rows<double>(int, int, const void*, int, double*, hipStream_t);
-template void dinv_rows<float>(int, int, const void*, int, float*, hipStream_t);
 
 // ---------------------------------------------------------------------------
 // Fused red-black Gauss-Seidel sweep (both colours in one pass, out of place).
@@ -2844,19 +2839,26 @@ template void rb_sweep<float>(const GridArgs&, const float*, const float*, const
                               int, int, const int*, double*, int, double, hipStream_t);
 
 // Per-estimate cache of the reciprocal coefficient 1/a = exp(-log a) at every
-// vertex of every row of one grid size.  A thread owns one (y, z) column:
-// S[k1] = sum_{k2,k3} c[k1,k2,k3] cos(pi k2 y) cos(pi k3 z) once, then K FMAs
-// and one FP64 exp per vertex along x (the KL sum written separably).  The
-// FP64 and/or FP32 copies are written in the same pass.
+// vertex of every row of every grid size.  A thread owns one (y, z) column:
+// S[k1] = sum_{k2,k3} c[k1,k2,k3] cos(pi k2 y) cos(pi k3 z) once, then K FMAs and
+// one FP64 exp per vertex along its x chunk (the KL sum written separably).  The
+// FP64 and/or FP32 copies are written in the same pass.  One launch covers all
+// grid sizes, and the columns are cut in x where the batch leaves the chip idle:
+// per grid and whole lines, the four grids of one 33^3 solve took 54 us.
 __global__ void __launch_bounds__(256)
-    k_coef_cache(int n, int rows, const double* __restrict__ coef, int K,
-                 const double* __restrict__ cosT, double* __restrict__ out64,
-                 float* __restrict__ out32, uint16_t* __restrict__ out16) {
+    k_coef_cache(FieldTable ft, const double* __restrict__ coef, int K) {
   __shared__ double sc[KMAX * KMAX * KMAX];
+  int lk = 0;
+  while (lk + 1 < ft.count && blockIdx.x >= (unsigned)ft.lv[lk + 1].cblk0) ++lk;   // uniform
+  const FieldLvl& L = ft.lv[lk];
+  const int n = L.n;
+  const double* __restrict__ cosT = L.cosT;
   const int cols = n * n;
   const int cpb = (cols + 255) / 256;
-  const int row = blockIdx.x / cpb;
-  const int col = (blockIdx.x - row * cpb) * 256 + threadIdx.x;
+  const int blk = (int)blockIdx.x - L.cblk0;
+  const int xc = blk % L.nxc, rb = blk / L.nxc;
+  const int row = rb / cpb;
+  const int col = (rb - row * cpb) * 256 + threadIdx.x;
   const int K3 = K * K * K;
   for (int j = threadIdx.x; j < K3; j += 256) sc[j] = coef[(size_t)row * K3 + j];
   __syncthreads();
@@ -2877,16 +2879,17 @@ __global__ void __launch_bounds__(256)
   }
   const int LP = lay_pitch(n);
   const size_t base = (size_t)row * (size_t)lay_row(n) + (size_t)iy * LP + iz + lay_off(n);
-  for (int ix = 0; ix < n; ++ix) {
+  const int x0 = xc * L.xch, x1 = min(n, x0 + L.xch);
+  for (int ix = x0; ix < x1; ++ix) {
     double l = 0.0;
 #pragma unroll
     for (int k = 0; k < KMAX; ++k)
       if (k < K) l += cosT[k * n + ix] * S[k];
     const double b = exp(-l);
     const size_t i = base + (size_t)ix * n * LP;
-    if (out64) out64[i] = b;
-    if (out32) out32[i] = (float)b;
-    if (out16) out16[i] = to_bf16((float)b);
+    if (L.c64) L.c64[i] = b;
+    if (L.c32) L.c32[i] = (float)b;
+    if (L.c16) L.c16[i] = to_bf16((float)b);
   }
 }
 
@@ -3007,12 +3010,37 @@ static int grid_for(long long total, int bs) {
   return (int)b;
 }
 
-void coef_cache(int n, int rows, const double* coef, int K, const double* cosT, double* out64,
-                float* out32, uint16_t* out16, hipStream_t s) {
-  if (rows <= 0 || (!out64 && !out32 && !out16)) return;
-  const int cpb = (n * n + 255) / 256;
-  hipLaunchKernelGGL(k_coef_cache, dim3(rows * cpb), dim3(256), 0, s, n, rows, coef, K, cosT,
-                     out64, out32, out16);
+void field_caches(FieldTable& ft, const double* coef, int K, hipStream_t s) {
+  long long cols = 0;   // workgroups of whole columns
+  for (int k = 0; k < ft.count; ++k)
+    cols += (long long)ft.lv[k].rows * cdiv((long long)ft.lv[k].n * ft.lv[k].n, 256);
+  long long cb = 0, db = 0;
+  bool d64 = false, d32 = false, d16 = false;
+  for (int k = 0; k < ft.count; ++k) {
+    FieldLvl& L = ft.lv[k];
+    // 2048 workgroups fill the chip; chunks of at least 4 planes
+    L.xch = cols >= 1024 ? L.n : std::max(4, (int)cdiv(L.n * std::max(cols, 1LL), 2048));
+    L.nxc = cdiv(L.n, L.xch);
+    L.cblk0 = (int)cb;
+    cb += (long long)L.rows * cdiv((long long)L.n * L.n, 256) * L.nxc;
+    L.dper = L.dinv ? cdiv(lay_row(L.n), DINV_CHUNK) : 0;
+    L.dblk0 = (int)db;
+    db += (long long)L.rows * L.dper;
+    if (L.dinv) {
+      if (L.c16) d16 = true;
+      else if (L.c32) d32 = true;
+      else d64 = true;
+    }
+  }
+  if (cb > 0)
+    hipLaunchKernelGGL(k_coef_cache, dim3((unsigned)cb), dim3(256), 0, s, ft, coef, K);
+  if (db <= 0) return;
+  if (d16)
+    hipLaunchKernelGGL((k_dinv<float, 2>), dim3((unsigned)db), dim3(256), 0, s, ft);
+  else if (d32)
+    hipLaunchKernelGGL((k_dinv<float, 1>), dim3((unsigned)db), dim3(256), 0, s, ft);
+  else if (d64)
+    hipLaunchKernelGGL((k_dinv<double, 1>), dim3((unsigned)db), dim3(256), 0, s, ft);
 }
 
 template <typename T>

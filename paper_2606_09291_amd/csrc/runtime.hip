@@ -504,14 +504,24 @@ void plan_fields(mlsgd_ctx* c, Plan* P) {
   kl_coeffs(P->d_level, P->d_sample, P->nprob, c->pb.seed, K, c->pb.kl_sigma2, c->pb.kl_law,
             c->pb.kl_rho, P->d_coef, c->stream);
   // the coefficient is regenerated from the draws once per call for the
-  // cached sweeps (the Krylov matvec and residual always run in FP64)
+  // cached sweeps (the Krylov matvec and residual always run in FP64); without
+  // multigrid only the problems' own grids are used, and no diagonals
+  const bool mg = c->pb.solver == MLSGD_SOLVER_MGPCG;
+  FieldTable ft{};
+  require(P->sizes.size() <= (size_t)MAX_SIZES, "too many grid sizes");
   for (auto& sl : P->sizes) {
-    coef_cache(sl.n, sl.rows, P->d_coef, K, sl.cosT, sl.C, sl.Cf, sl.Cb, c->stream);
-    if (sl.Di) dinv_rows<double>(sl.n, sl.rows, sl.C, 0, sl.Di, c->stream);
-    if (sl.Dif)
-      dinv_rows<float>(sl.n, sl.rows, sl.Cb ? (const void*)sl.Cb : (const void*)sl.Cf,
-                       sl.Cb ? 1 : 0, sl.Dif, c->stream);
+    const bool top = sl.top_begin < sl.rows;
+    if (sl.rows <= 0 || (!mg && !top) || !(sl.C || sl.Cf || sl.Cb)) continue;
+    FieldLvl& f = ft.lv[ft.count++];
+    f.n = sl.n;
+    f.rows = sl.rows;
+    f.cosT = sl.cosT;
+    f.c64 = sl.C;
+    f.c32 = sl.Cf;
+    f.c16 = sl.Cb;
+    if (mg) f.dinv = sl.Di ? (void*)sl.Di : (void*)sl.Dif;
   }
+  field_caches(ft, P->d_coef, K, c->stream);
   if (P->dense_N) {
     const SizeLvl& co = P->sizes.back();
     dense_coarse_inv(co.n, co.rows, P->d_coef, K, co.cosT, P->ainv, P->dwork, c->stream);
