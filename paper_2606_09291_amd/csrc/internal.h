@@ -147,12 +147,15 @@ inline bool pre2r_half_tiles(const GridArgs& g) {
   if (g.v.R > 0) return g.v.xchunk >= g.n - 2 || (g.v.xchunk & 1) == 0;
   return g.t.nxc == 1 || (g.t.xchunk & 1) == 0;
 }
+// with half, march_pre2r writes the coarse grid's right-hand side itself
+inline bool pre2r_to_coarse(const GridArgs& g) { return g.v.R > 0 && g.v.full; }
 // the same two steps and the residual of their result in one pass:
 // xout = J(omega2) J(omega1) 0, rout = b - A xout (tiles and coefficient as
-// fused_tiles; returns false, launching nothing, otherwise).  half: rout
-// receives instead the x part of the full-weighting restriction of the
-// residual, plane I = r(2I-1)/4 + r(2I)/2 + r(2I+1)/4 at interior columns, for
-// restrict_yz_rows (also needs pre2r_half_tiles)
+// fused_tiles; returns false, launching nothing, otherwise).  half (also needs
+// pre2r_half_tiles): rout receives instead the full-weighting restriction of the
+// residual (the coarse grid's right-hand-side rows) where pre2r_to_coarse, else
+// its x part, plane I = r(2I-1)/4 + r(2I)/2 + r(2I+1)/4 at interior columns, for
+// restrict_yz_rows
 template <typename T>
 bool march_pre2r(const GridArgs& g, const T* dinv, const T* b, T* xout, T* rout, double omega1,
                  double omega2, bool half, hipStream_t s);

@@ -851,15 +851,15 @@ void vcycle_cheb(mlsgd_ctx* c, Plan* P, int k0 = 0, int rlim = INT_MAX, bool xin
       // and in A[0] r or (half) r restricted along x, then the rest of the
       // restriction
       const bool half = c->pre2r_half && pre2r_half_tiles(g);
+      const bool direct = half && pre2r_to_coarse(g);   // the whole restriction too
+      T* const bc = mg_view<T>(P->sizes[k + 1]).B;
       timed_launch(c, g, pre2r_bytes<T>(L.n, g.rows, half), [&] {
-        march_pre2r<T>(g, dinv, v.B, A[1], A[0], om[0], om[1], half, c->stream);
+        march_pre2r<T>(g, dinv, v.B, A[1], direct ? bc : A[0], om[0], om[1], half, c->stream);
       }, 3);
-      if (half)
-        restrict_yz_rows<T>(L.n, g.rows, 0, P->d_scal, A[0], mg_view<T>(P->sizes[k + 1]).B,
-                            c->stream);
-      else
-        restrict_rows<T>(L.n, g.rows, 0, P->d_scal, A[0], mg_view<T>(P->sizes[k + 1]).B,
-                         c->stream);
+      if (!half)
+        restrict_rows<T>(L.n, g.rows, 0, P->d_scal, A[0], bc, c->stream);
+      else if (!direct)
+        restrict_yz_rows<T>(L.n, g.rows, 0, P->d_scal, A[0], bc, c->stream);
       L.cur = 1;
       continue;
     }
