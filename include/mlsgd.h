@@ -321,7 +321,9 @@ int mlsgd_set_graph(mlsgd_ctx* ctx, int enable);
  * smoothing step (enable = 1), the fused two-step post-smoothing pass
  * (enable = 2), the fused pre-smoothing pass with its residual (enable = 3)
  * or the Krylov matvec (enable = 4); the fused passes run on grids with
- * 64-wide tiles of height 8 or 16 and a cached coefficient.  The call
+ * 64-wide tiles of height 8 or 16 and a cached coefficient.  While a grid of
+ * at most 17 vertices is timed, its passes run one by one where one kernel
+ * would do their work together (results then differ by rounding).  The call
  * first returns the totals accumulated so far (host outputs, nullable:
  * summed milliseconds, launch count, algorithmic bytes = interior points x
  * bytes the kernel must move, the coefficient counted at 0 bytes since the

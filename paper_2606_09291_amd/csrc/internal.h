@@ -185,6 +185,22 @@ void vcycle_small(int rows, const double* om, int deg, int top_begin, const CgSc
                   const T* b9, const void* c9, const void* c5, const void* c3, int cache_bf16,
                   T* xout, const int* poff, double* partial, bool start, hipStream_t s);
 
+// The same from 17^3 down, a workgroup per problem: rows 0 .. rows17-1 of the
+// 17^3 rows, and of the 9^3 rows those from rows17 to rows9-1 (top grid 9^3).  <b, z>
+// of the problems >= top17 goes to the first of their `slots` partial slots.
+// The rows of 17^3 and 9^3 are dense.
+template <typename T>
+struct MidArgs {
+  int rows17, rows9, top17, slots;
+  const T *b17, *b9;
+  const void *c17, *c9, *c5, *c3;
+  T *x17, *x9;
+};
+constexpr int VM_ROWS = 1024;   // most rows17 it is used for
+template <typename T>
+void vcycle_mid(const double* om, int deg, int top9, const CgScal* scal, const MidArgs<T>& ma,
+                int cache_bf16, const int* poff, double* partial, bool start, hipStream_t s);
+
 // Whole unpreconditioned CG solves, one workgroup each, of `rows` problems on an
 // n^3 grid (n <= CG_SMALL_MAX) with the cached FP64 1/a: right-hand-side rows
 // in, solution rows out (interior vertices), and the problems' scalars

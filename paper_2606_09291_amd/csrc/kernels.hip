@@ -2154,9 +2154,8 @@ struct VsWave {
     const int i = on5 ? lane : 0;
     o5 = ((1 + i / 9) * 5 + 1 + (i / 3) % 3) * 5 + 1 + i % 3;
   }
-  // faces and reciprocal diagonals of the three grids from their cached 1/a,
-  // then zero value arrays
-  __device__ void coefficients(const CR* c9, const CR* c5, const CR* c3) {
+  // cached 1/a of the three grids
+  __device__ void load(const CR* c9, const CR* c5, const CR* c3) {
     for (int v = lane; v < 729; v += 64) s.v9[v] = cvt(c9[v]);
     for (int v = lane; v < 125; v += 64) s.v5[v] = cvt(c5[v]);
     T f3 = T(0);
@@ -2168,6 +2167,9 @@ struct VsWave {
     }
     di3 = drcp(T(4) * f3);
     wave_sync();
+  }
+  // faces and reciprocal diagonals from them, then zero value arrays
+  __device__ void coefficients() {
 #pragma unroll
     for (int k = 0; k < 8; ++k) fx[k] = face(s.v9[o9 + (k - 1) * 81], s.v9[o9 + k * 81]);
 #pragma unroll
@@ -2316,44 +2318,47 @@ struct VsWave {
     prolong5(false);
     for (int j = va.deg - 1; j >= 0; --j) jac9((T)va.om[j]);
   }
+  // START: the full-multigrid start of the three grids instead of a cycle from zero
+  template <bool START>
+  __device__ void solve(const VsArgs& va) {
+    if constexpr (START) {
+      // b on 5^3 and 3^3, the exact 3^3 solution, then one cycle a grid from the
+      // prolonged solution of the grid below
+      restrict9(b);
+      x5 = prolong3(solve3(b5));
+      for (int j = 0; j < va.deg; ++j) jac5((T)va.om[j]);
+      coarse5(va);
+      prolong5(true);
+      for (int j = 0; j < va.deg; ++j) jac9((T)va.om[j]);
+    } else {
+#pragma unroll
+      for (int k = 0; k < 7; ++k) x[k] = (T)va.om[0] * (b[k] * di[k]);
+      for (int j = 1; j < va.deg; ++j) jac9((T)va.om[j]);
+    }
+    coarse9(va);
+  }
 };
 
-// START: the full-multigrid start of the three grids instead of a cycle from zero
+// One problem of k_vsmall, by one wave.
 template <typename T, int CK, bool START>
-__global__ void __launch_bounds__(64 * VS_WAVES)
-    k_vsmall(VsArgs va, int rows, const CgScal* __restrict__ scal, const T* __restrict__ b9,
-             const void* __restrict__ c9, const void* __restrict__ c5,
-             const void* __restrict__ c3, T* __restrict__ xout, const int* __restrict__ poff,
-             double* __restrict__ partial) {
+__device__ __forceinline__ void vs_problem(VsLds<T>& lds, int lane, int prob, const VsArgs& va,
+                                           const T* __restrict__ b9, const void* __restrict__ c9,
+                                           const void* __restrict__ c5,
+                                           const void* __restrict__ c3, T* __restrict__ xout,
+                                           const int* __restrict__ poff,
+                                           double* __restrict__ partial) {
   using CR = typename VsWave<T, CK>::CR;
-  __shared__ VsLds<T> lds[VS_WAVES];
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int prob = blockIdx.x * VS_WAVES + wave;
-  if (prob >= rows || (scal && !scal[prob].active)) return;  // uniform per wave, no barriers
-  VsWave<T, CK> w(lds[wave], lane);
+  VsWave<T, CK> w(lds, lane);
   const T* brow = b9 + (size_t)prob * 729;
 #pragma unroll
   for (int k = 0; k < 7; ++k) {
     const T v = brow[w.o9 + k * 81];
     w.b[k] = w.on9 ? v : T(0);
   }
-  w.coefficients((const CR*)c9 + (size_t)prob * 729, (const CR*)c5 + (size_t)prob * 125,
-                 (const CR*)c3 + (size_t)prob * 27);
-  if constexpr (START) {
-    // b on 5^3 and 3^3, the exact 3^3 solution, then one cycle a grid from the
-    // prolonged solution of the grid below
-    w.restrict9(w.b);
-    w.x5 = w.prolong3(w.solve3(w.b5));
-    for (int j = 0; j < va.deg; ++j) w.jac5((T)va.om[j]);
-    w.coarse5(va);
-    w.prolong5(true);
-    for (int j = 0; j < va.deg; ++j) w.jac9((T)va.om[j]);
-  } else {
-#pragma unroll
-    for (int k = 0; k < 7; ++k) w.x[k] = (T)va.om[0] * (w.b[k] * w.di[k]);
-    for (int j = 1; j < va.deg; ++j) w.jac9((T)va.om[j]);
-  }
-  w.coarse9(va);
+  w.load((const CR*)c9 + (size_t)prob * 729, (const CR*)c5 + (size_t)prob * 125,
+         (const CR*)c3 + (size_t)prob * 27);
+  w.coefficients();
+  w.template solve<START>(va);
   T* xrow = xout + (size_t)prob * 729;
   if (w.on9) {
 #pragma unroll
@@ -2369,6 +2374,267 @@ __global__ void __launch_bounds__(64 * VS_WAVES)
     if (lane == 63) partial[poff[prob]] = dot;
   }
 }
+
+template <typename T, int CK, bool START>
+__global__ void __launch_bounds__(64 * VS_WAVES)
+    k_vsmall(VsArgs va, int rows, const CgScal* __restrict__ scal, const T* __restrict__ b9,
+             const void* __restrict__ c9, const void* __restrict__ c5,
+             const void* __restrict__ c3, T* __restrict__ xout, const int* __restrict__ poff,
+             double* __restrict__ partial) {
+  __shared__ VsLds<T> lds[VS_WAVES];
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int prob = blockIdx.x * VS_WAVES + wave;
+  if (prob >= rows || (scal && !scal[prob].active)) return;  // uniform per wave, no barriers
+  vs_problem<T, CK, START>(lds[wave], lane, prob, va, b9, c9, c5, c3, xout, poff, partial);
+}
+
+// The same cycle (START: start) from 17^3 down for batches that leave the chip
+// idle: one workgroup per problem, eight waves on the 17^3 grid and a ninth on
+// the grids below it, in place of a pre-smoothing, a k_vsmall and a
+// post-smoothing launch that each wait for their loads and form their faces
+// anew.  A thread holds eight x points of a 17^3 column in registers (faces,
+// right-hand side, iterate, reciprocal diagonal); LDS passes values to the
+// neighbouring columns through two buffers in turn, one barrier a step.  The
+// ninth wave prepares its coefficients meanwhile and runs its part between two
+// barriers; both roles meet every barrier (the counts are noted at each).
+// Problems whose top grid is 9^3 (rows17 and on) take a wave each.
+// Two register sets (the 17^3 waves' 130 and the ninth's 200) share 168 VGPRs a
+// lane; the compiler keeps some thirty of the ninth wave's values in scratch.
+// Gradients on one level of 17^3, 64 / 256 / 512 samples: FP64 1.31 -> 1.07,
+// 1.83 -> 1.44, 2.49 -> 2.25 ms; FP32 cycles 1.28 -> 0.95, 1.68 -> 1.30,
+// 2.27 -> 1.98; one 33^3 solve and adjoint 1.67 -> 1.46 ms.
+constexpr int VM_FINE = 512;   // threads on the 17^3 grid
+constexpr int VM_WAVES = VM_FINE / 64 + 1;
+constexpr int VM_XS = 8, VM_P = 17, VM_PP = VM_P * VM_P, VM_N = VM_P * VM_PP;
+
+template <typename T, int CK, bool START>
+__global__ void __launch_bounds__(64 * VM_WAVES)
+    k_vmid(VsArgs va, MidArgs<T> ma, const CgScal* __restrict__ scal,
+           const int* __restrict__ poff, double* __restrict__ partial) {
+  using CR = typename VsWave<T, CK>::CR;
+  __shared__ T v17[2][VM_N];
+  __shared__ T rb[343];             // right-hand side of 9^3
+  __shared__ VsLds<T> lds;
+  __shared__ double sred[VM_FINE / 64];
+  const int prob = blockIdx.x;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  if (prob >= ma.rows17) {
+    const int pw = ma.rows17 + (prob - ma.rows17) * VM_WAVES + wave;
+    if (pw >= ma.rows9 || (scal && !scal[pw].active)) return;   // uniform per wave, no barriers
+    static_assert(VM_WAVES * sizeof(VsLds<T>) <= sizeof(v17), "");
+    vs_problem<T, CK, START>(reinterpret_cast<VsLds<T>*>(&v17[0][0])[wave], threadIdx.x & 63, pw,
+                             va, ma.b9, ma.c9, ma.c5, ma.c3, ma.x9, poff, partial);
+    return;
+  }
+  if (scal && !scal[prob].active) return;   // uniform per workgroup
+  const int npre = START ? va.deg : va.deg - 1;   // pre-smoothing steps that read neighbours
+
+  if (wave == VM_FINE / 64) {
+    const int lane = threadIdx.x & 63;
+    VsWave<T, CK> w(lds, lane);
+    const int rl = w.on9 ? (lane >> 3) * 7 + (lane & 7) : 0;
+    auto rhs = [&] {
+#pragma unroll
+      for (int k = 0; k < 7; ++k) w.b[k] = w.on9 ? rb[k * 49 + rl] : T(0);
+    };
+    w.load((const CR*)ma.c9 + (size_t)prob * 729, (const CR*)ma.c5 + (size_t)prob * 125,
+           (const CR*)ma.c3 + (size_t)prob * 27);
+    __syncthreads();   // 1/a of 17^3 in LDS
+    w.coefficients();
+    __syncthreads();   // 17^3 faces formed
+    if constexpr (START) {
+      __syncthreads();   // b published
+      __syncthreads();   // b of 9^3 in rb
+      rhs();
+      w.template solve<true>(va);
+      w.put9(w.x);
+      __syncthreads();   // start of 9^3 in lds.v9
+    }
+    for (int j = 0; j < npre + 2; ++j) __syncthreads();   // steps, x and r published
+    __syncthreads();   // right-hand side of 9^3 in rb
+    rhs();
+    w.template solve<false>(va);
+    w.put9(w.x);
+    __syncthreads();   // correction of 9^3 in lds.v9
+    for (int j = 0; j < va.deg; ++j) __syncthreads();   // post-smoothing
+    __syncthreads();   // wave sums
+    return;
+  }
+
+  const int tid = threadIdx.x;
+  const int iz = tid & 15, iy = (tid >> 4) & 15, x0 = 1 + VM_XS * (tid >> 8);
+  const int l0 = (x0 * VM_P + iy) * VM_P + iz;   // vertex of the first own point
+  const T ih2 = T(256);
+  const CR* __restrict__ c = (const CR*)ma.c17 + (size_t)prob * VM_N;
+  const T* __restrict__ brow = ma.b17 + (size_t)prob * VM_N;
+  T b[VM_XS], x[VM_XS], di[VM_XS];
+  T fx[VM_XS + 1], fym[VM_XS], fyp[VM_XS], fzm[VM_XS], fzp[VM_XS];
+  bool own[VM_XS];
+#pragma unroll
+  for (int j = 0; j < VM_XS; ++j) {
+    own[j] = iy >= 1 && iz >= 1 && x0 + j <= 15;
+    b[j] = own[j] ? brow[l0 + j * VM_PP] : T(0);
+  }
+  for (int v = tid; v < VM_N; v += VM_FINE) {
+    v17[1][v] = VsWave<T, CK>::cvt(c[v]);
+    v17[0][v] = T(0);
+  }
+  __syncthreads();   // 1/a in LDS
+  {
+    // (planes beyond the grid stand for points that are not owned)
+    auto bp = [&](int j) { return &v17[1][l0 + (x0 + j <= 16 ? j : 16 - x0) * VM_PP]; };
+#pragma unroll
+    for (int j = 0; j <= VM_XS; ++j) fx[j] = sface(*bp(j - 1), *bp(j));
+#pragma unroll
+    for (int j = 0; j < VM_XS; ++j) {
+      const T* p = bp(j);
+      fym[j] = sface(p[0], p[-VM_P]);
+      // (the last plane's row past the grid is the boundary row itself)
+      fyp[j] = sface(p[0], p[VM_P]);
+      fzp[j] = sface(p[0], p[1]);
+      fzm[j] = __shfl_up(fzp[j], 1, 16);   // of lane iz - 1
+      di[j] = srcp(ih2 * (((fx[j] + fx[j + 1]) + (fym[j] + fyp[j])) + (fzm[j] + fzp[j])));
+    }
+  }
+  __syncthreads();   // faces formed
+  for (int v = tid; v < VM_N; v += VM_FINE) v17[1][v] = T(0);
+  int q = 0;
+  const T* vq = nullptr;   // the values published last
+  auto publish = [&](const T (&v)[VM_XS]) {   // one barrier
+#pragma unroll
+    for (int j = 0; j < VM_XS; ++j)
+      if (own[j]) v17[q][l0 + j * VM_PP] = v[j];
+    vq = &v17[q][l0];
+    __syncthreads();
+    q ^= 1;
+  };
+  // sum of faces times neighbours, x published
+  const int up = x0 + VM_XS <= 16 ? VM_XS * VM_PP : 0;
+  auto off = [&](int j, T lo, T hi) {
+    const T xm = j > 0 ? x[j > 0 ? j - 1 : 0] : lo;
+    const T xp = j < VM_XS - 1 ? x[j < VM_XS - 1 ? j + 1 : 0] : hi;
+    const T* p = vq + j * VM_PP;
+    return ((fx[j] * xm + fx[j + 1] * xp) + (fym[j] * p[-VM_P] + fyp[j] * p[VM_P])) +
+           (fzm[j] * p[-1] + fzp[j] * p[1]);
+  };
+  auto jac = [&](T om) {   // x <- x + omega D^-1 (b - A x)
+    publish(x);
+    const T lo = vq[-VM_PP], hi = vq[up];
+    T y[VM_XS];
+#pragma unroll
+    for (int j = 0; j < VM_XS; ++j)
+      y[j] = own[j] ? x[j] + om * ((b[j] + ih2 * off(j, lo, hi)) * di[j] - x[j]) : T(0);
+#pragma unroll
+    for (int j = 0; j < VM_XS; ++j) x[j] = y[j];
+  };
+  auto restrict17 = [&](const T (&v)[VM_XS]) {   // full weighting into rb; two barriers
+    publish(v);
+    const T* u = vq - l0;
+    if (tid < 343) {
+      const int e = (2 * (1 + tid / 49) * VM_P + 2 * (1 + (tid / 7) % 7)) * VM_P + 2 * (1 + tid % 7);
+      T acc = T(0);
+#pragma unroll
+      for (int dx = -1; dx <= 1; ++dx) {
+        T ay = T(0);
+#pragma unroll
+        for (int dy = -1; dy <= 1; ++dy) {
+          const T* p = u + e + dx * VM_PP + dy * VM_P;
+          ay += (dy == 0 ? T(0.5) : T(0.25)) * (T(0.25) * p[-1] + T(0.5) * p[0] + T(0.25) * p[1]);
+        }
+        acc += (dx == 0 ? T(0.5) : T(0.25)) * ay;
+      }
+      rb[tid] = acc;
+    }
+    __syncthreads();
+  };
+  auto prolong9 = [&](bool set) {   // the 9^3 values added to x, or (set) as x
+    const int dy = (iy & 1) ? 9 : 0, dz = iz & 1;
+    const T* p = &lds.v9[(x0 >> 1) * 81 + (iy >> 1) * 9 + (iz >> 1)];
+    T w[5];
+#pragma unroll
+    for (int j = 0; j < 5; ++j)
+      w[j] = T(0.25) * ((p[j * 81] + p[j * 81 + dz]) + (p[j * 81 + dy] + p[j * 81 + dy + dz]));
+#pragma unroll
+    for (int j = 0; j < VM_XS; ++j) {
+      const T v = (j & 1) ? w[(j + 1) / 2] : T(0.5) * (w[j / 2] + w[j / 2 + 1]);
+      x[j] = own[j] ? (set ? v : x[j] + v) : T(0);
+    }
+  };
+  if constexpr (START) {
+    restrict17(b);      // b published, b of 9^3 in rb
+    __syncthreads();    // start of 9^3 in lds.v9
+    prolong9(true);
+    for (int j = 0; j < va.deg; ++j) jac((T)va.om[j]);
+  } else {
+#pragma unroll
+    for (int j = 0; j < VM_XS; ++j) x[j] = own[j] ? (T)va.om[0] * (b[j] * di[j]) : T(0);
+    for (int j = 1; j < va.deg; ++j) jac((T)va.om[j]);
+  }
+  {
+    publish(x);
+    const T lo = vq[-VM_PP], hi = vq[up];
+    T r[VM_XS];
+#pragma unroll
+    for (int j = 0; j < VM_XS; ++j) {
+      const T diag = ((fx[j] + fx[j + 1]) + (fym[j] + fyp[j])) + (fzm[j] + fzp[j]);
+      r[j] = own[j] ? b[j] - ih2 * (diag * x[j] - off(j, lo, hi)) : T(0);
+    }
+    restrict17(r);      // r published, right-hand side of 9^3 in rb
+  }
+  __syncthreads();      // correction of 9^3 in lds.v9
+  prolong9(false);
+  for (int j = va.deg - 1; j >= 0; --j) jac((T)va.om[j]);
+  T* xrow = ma.x17 + (size_t)prob * VM_N;
+#pragma unroll
+  for (int j = 0; j < VM_XS; ++j)
+    if (own[j]) xrow[l0 + j * VM_PP] = x[j];
+  const bool sum = partial != nullptr && prob >= ma.top17;
+  if (sum) {
+    double dot = 0.0;
+#pragma unroll
+    for (int j = 0; j < VM_XS; ++j) dot += (double)b[j] * (double)x[j];
+    dot = wave_sum63(dot);
+    if ((tid & 63) == 63) sred[wave] = dot;
+  }
+  __syncthreads();      // wave sums
+  if (sum && tid < ma.slots) {
+    double t = 0.0;
+#pragma unroll
+    for (int w = 0; w < VM_FINE / 64; ++w) t += sred[w];
+    partial[poff[prob] + tid] = tid == 0 ? t : 0.0;
+  }
+}
+
+template <typename T>
+void vcycle_mid(const double* om, int deg, int top9, const CgScal* scal, const MidArgs<T>& ma,
+                int cache_bf16, const int* poff, double* partial, bool start, hipStream_t s) {
+  if (ma.rows9 <= 0) return;
+  VsArgs va{};
+  for (int j = 0; j < deg && j < VS_MAXDEG; ++j) va.om[j] = om[j];
+  va.deg = deg;
+  va.top_begin = top9;
+#define MLSGD_LAUNCH(CK_, START_)                                                              \
+  hipLaunchKernelGGL((k_vmid<T, CK_, START_>),                                                 \
+                     dim3(ma.rows17 + cdiv(ma.rows9 - ma.rows17, VM_WAVES)), dim3(64 * VM_WAVES), 0, \
+                     s, va, ma, scal, poff, partial)
+  if (sizeof(T) == 4 && cache_bf16) {
+    if constexpr (sizeof(T) == 4) {
+      if (start)
+        MLSGD_LAUNCH(2, true);
+      else
+        MLSGD_LAUNCH(2, false);
+    }
+  } else if (start) {
+    MLSGD_LAUNCH(1, true);
+  } else {
+    MLSGD_LAUNCH(1, false);
+  }
+#undef MLSGD_LAUNCH
+}
+template void vcycle_mid<double>(const double*, int, int, const CgScal*, const MidArgs<double>&, int,
+                                 const int*, double*, bool, hipStream_t);
+template void vcycle_mid<float>(const double*, int, int, const CgScal*, const MidArgs<float>&, int,
+                                const int*, double*, bool, hipStream_t);
 
 template <typename T>
 void vcycle_small(int rows, const double* om, int deg, int top_begin, const CgScal* scal,

@@ -779,6 +779,49 @@ bool small_cycle(mlsgd_ctx* c, Plan* P) {
   return true;
 }
 
+// The one-kernel cycle from 17^3 down applies, above it, to few problems: a
+// workgroup of it fills a CU, so its time grows by a round for every 256 rows
+// of 17^3, where the separate passes fill the chip better and better.  Both
+// meet between 1024 and 1536 rows (gradients on one level of 17^3, separate
+// against one kernel: 1024 samples 3.93 / 3.75 ms, 1536 5.61 / 5.90; FP32 cycles
+// 3.39 / 3.20, 5.15 / 5.23).  Event timing of the passes on 17^3 keeps them.
+template <typename T>
+bool mid_cycle(mlsgd_ctx* c, Plan* P) {
+  const int S = (int)P->sizes.size();
+  if (S < 4 || (c->tm.on && c->tm.n == 17) || !small_cycle<T>(c, P)) return false;
+  const SizeLvl& L = P->sizes[S - 4];
+  return L.n == 17 && L.rows <= VM_ROWS &&
+         (sizeof(T) == 8 ? args_size(c, P, L) : args_size32(c, P, L)).cache;
+}
+
+// One cycle from 17^3 down (start: the full-multigrid start) over the first
+// `rlim` problems; both grids' iterates end in X.
+template <typename T>
+void mid_run(mlsgd_ctx* c, Plan* P, const std::vector<double>& om, int rlim, bool start) {
+  const int S = (int)P->sizes.size();
+  SizeLvl &L17 = P->sizes[S - 4], &L9 = P->sizes[S - 3];
+  auto cache = [&](const SizeLvl& L) {
+    return (sizeof(T) == 8 ? args_size(c, P, L) : args_size32(c, P, L)).cache;
+  };
+  const MgView<T> v17 = mg_view<T>(L17), v9 = mg_view<T>(L9);
+  MidArgs<T> ma{};
+  ma.rows17 = std::min(L17.rows, rlim);
+  ma.rows9 = std::min(L9.rows, rlim);
+  ma.top17 = L17.top_begin;
+  ma.slots = L17.vslots;
+  ma.b17 = v17.B;
+  ma.b9 = v9.B;
+  ma.c17 = cache(L17);
+  ma.c9 = cache(L9);
+  ma.c5 = cache(P->sizes[S - 2]);
+  ma.c3 = cache(P->sizes[S - 1]);
+  ma.x17 = v17.X;
+  ma.x9 = v9.X;
+  vcycle_mid<T>(om.data(), c->nu, L9.top_begin, P->d_scal, ma, sizeof(T) == 4 && L17.Cb, P->d_poff,
+                start ? nullptr : P->d_partial, start, c->stream);
+  L17.cur = L9.cur = 0;
+}
+
 //
 // k0, rlim, xinit serve the full-multigrid start: the cycle then begins on
 // grid size k0, covers rows 0 .. rlim-1 of every size (the problems whose top
@@ -794,14 +837,23 @@ void vcycle_cheb(mlsgd_ctx* c, Plan* P, int k0 = 0, int rlim = INT_MAX, bool xin
     g.rows = std::min(g.rows, rlim);
     return g;
   };
-  // the levels from 9^3 down run as one kernel where small_cycle allows
+  // the levels from 17^3 or 9^3 down run as one kernel where mid_cycle or
+  // small_cycle allows
   int ks = S;
-  if (small_cycle<T>(c, P) && S - 3 >= k0 && !(xinit && S - 3 == k0)) ks = S - 3;
+  const bool mid = mid_cycle<T>(c, P);
+  if (mid && S - 4 >= k0 && !(xinit && S - 4 == k0))
+    ks = S - 4;
+  else if (small_cycle<T>(c, P) && S - 3 >= k0 && !(xinit && S - 3 == k0))
+    ks = S - 3;
   for (int k = k0; k < S; ++k) {
     SizeLvl& L = P->sizes[k];
     MgView<T> v = mg_view<T>(L);
     T* A[2] = {v.X, v.R};
     GridArgs g = args(L);
+    if (k == ks && k == S - 4) {
+      mid_run<T>(c, P, om, rlim, false);
+      break;
+    }
     if (k == ks) {
       const GridArgs g5 = args(P->sizes[k + 1]), g3 = args(P->sizes[k + 2]);
       vcycle_small<T>(g.rows, om.data(), deg, L.top_begin, P->d_scal, v.B, g.cache, g5.cache,
@@ -885,7 +937,7 @@ void vcycle_cheb(mlsgd_ctx* c, Plan* P, int k0 = 0, int rlim = INT_MAX, bool xin
                      c->stream);
     L.cur = cur;
   }
-  // up from the level above the coarsest one handled (the small cycle's 9^3, or S - 1)
+  // up from the level above the coarsest one handled (the one-kernel cycle's, or S - 1)
   for (int k = (ks < S ? ks : S - 1) - 1; k >= k0; --k) {
     SizeLvl& L = P->sizes[k];
     MgView<T> v = mg_view<T>(L);
@@ -1100,8 +1152,8 @@ void fmg_start(mlsgd_ctx* c, Plan* P) {
     }
   }
   // kb: the largest grid whose start is ready
-  const bool small = small_cycle<T>(c, P);
-  const int kb = small ? S - 3 : S - 1;
+  const bool small = small_cycle<T>(c, P), mid = mid_cycle<T>(c, P);
+  const int kb = mid ? S - 4 : small ? S - 3 : S - 1;
   for (int k = 0; k < kb; ++k) {
     SizeLvl& L = P->sizes[k];
     restrict_rows<T>(L.n, L.rows, 0, nullptr, mg_view<T>(L).B, mg_view<T>(P->sizes[k + 1]).B, s);
@@ -1119,7 +1171,10 @@ void fmg_start(mlsgd_ctx* c, Plan* P) {
   };
   {
     SizeLvl& L = P->sizes[kb];
-    if (small) {   // 3^3, 5^3 and 9^3 in one kernel
+    if (mid) {   // 3^3 .. 17^3 in one kernel
+      mid_run<T>(c, P, cheb_omegas(c->nu, c->cheb_lo), INT_MAX, true);
+      start(kb + 1);
+    } else if (small) {   // 3^3, 5^3 and 9^3 in one kernel
       const std::vector<double> om = cheb_omegas(c->nu, c->cheb_lo);
       const GridArgs g9 = args(L), g5 = args(P->sizes[S - 2]), g3 = args(P->sizes[S - 1]);
       vcycle_small<T>(L.rows, om.data(), c->nu, 0, P->d_scal, mg_view<T>(L).B, g9.cache, g5.cache,
@@ -1212,12 +1267,12 @@ void flush_steps(mlsgd_ctx* c, Plan* P) {
 }
 
 // Plain CG where every top grid is small enough for one workgroup: whole
-// solves as one launch per grid size, no host reads.  The event timing of the
-// matvec and the forced restarts are the level-by-level path's.
+// solves as one launch per grid size, no host reads.  Event timing of the
+// matvec on such a grid and the forced restarts keep the level-by-level path.
 bool cg_small_applies(const mlsgd_ctx* c, const Plan* P) {
-  if (c->pb.solver != MLSGD_SOLVER_CG || c->tm.on || c->force_restart) return false;
+  if (c->pb.solver != MLSGD_SOLVER_CG || c->force_restart) return false;
   for (const auto& gr : P->groups)
-    if (gr.n > CG_SMALL_MAX || !P->sizes[gr.sl].C) return false;
+    if (gr.n > CG_SMALL_MAX || !P->sizes[gr.sl].C || (c->tm.on && c->tm.n == gr.n)) return false;
   return true;
 }
 
