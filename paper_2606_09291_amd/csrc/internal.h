@@ -269,13 +269,48 @@ void group_dot(const GridArgs& g, const double* a, const double* b, const int* p
 void group_update(const GridArgs& g, double* x, const double* p, double* r,
                   const double* q, const int* poff, double* partial, float* r32,
                   hipStream_t s);
-// r -= alpha q and <r, r> (x is updated by the next matvec or group_xflush)
-void group_rupdate(const GridArgs& g, double* r, const double* q, const int* poff,
-                   double* partial, float* r32, hipStream_t s);
-// x += alpha p for every problem with a pending step, p from buffer p0 or p1
-// as its scalars record (g.scal must be set; active or not)
-void group_xflush(const GridArgs& g, double* x, const double* p0, const double* p1,
-                  hipStream_t s);
+// The rows of every group, for the ops that take them in one launch (`begin`,
+// the first workgroup, is the launch's to fill in).
+constexpr int MAX_GROUPS = 8;
+struct GroupRows {
+  GridArgs g;
+  double* a;
+  const double* b;
+  double* c;
+  const double* d;
+  float* cf;
+  int begin;
+};
+struct GroupTable {
+  GroupRows gr[MAX_GROUPS];
+  int count;
+};
+// c -= alpha d (r, q), cf (nullable) = c in FP32, and <c, c> (x is updated by
+// the next matvec or group_xflush)
+void group_rupdate(GroupTable& t, const int* poff, double* partial, hipStream_t s);
+// a += alpha p (a: x) for every problem with a pending step, p from buffer b or
+// d as its scalars record (g.scal must be set; active or not)
+void group_xflush(GroupTable& t, hipStream_t s);
+// The FP64 marching ops over every group in one launch, for groups that
+// group_tiles allows: the matvec (in: z, in2: p_old, out: q, out2: p_new, xdef: x
+// or null) and the residual (in: x, rhs: b, out: r or null; partials of its norm
+// where `partial` is given)
+struct MarchGroup {
+  GridArgs g;
+  const void* in;
+  const double *in2, *rhs;
+  double *out, *out2, *xdef;
+  int begin;
+};
+struct MarchTable {
+  MarchGroup gr[MAX_GROUPS];
+  int count;
+};
+inline bool group_tiles(const GridArgs& g) {
+  return g.cache != nullptr && (g.t.TZ != 64 || g.t.TY == 8);
+}
+void matvec_groups(MarchTable& t, bool z32, const int* poff, double* partial, hipStream_t s);
+void resid_groups(MarchTable& t, const int* poff, double* partial, hipStream_t s);
 // b = y - y_d on the interior (y_d dense), y reset to 0, partials of |b|^2
 void group_misfit(const GridArgs& g, double* y, const double* yd, double* b_rows,
                   const int* poff, double* partial, hipStream_t s);

@@ -122,19 +122,23 @@ __device__ __forceinline__ double wave_sum63(double v) {
 }
 
 template <int NT>
-__device__ __forceinline__ double block_sum(double v, double* sred) {
+__device__ __forceinline__ double block_sum(double v, double* sred, int tid) {
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) v += __shfl_down(v, o, 64);
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const int lane = tid & 63, w = tid >> 6;
   if (lane == 0) sred[w] = v;
   __syncthreads();
   double s = 0.0;
-  if (threadIdx.x == 0) {
+  if (tid == 0) {
 #pragma unroll
     for (int i = 0; i < NT / 64; ++i) s += sred[i];
   }
   __syncthreads();
   return s;  // valid in thread 0
+}
+template <int NT>
+__device__ __forceinline__ double block_sum(double v, double* sred) {
+  return block_sum<NT>(v, sred, threadIdx.x);
 }
 
 static inline int cdiv(long long a, long long b) { return (int)((a + b - 1) / b); }
@@ -292,23 +296,35 @@ struct Ld {
 
 enum MarchOp { OP_RESID = 0, OP_MATVEC = 1, OP_GS = 2, OP_JAC = 3, OP_JACP = 4, OP_JAC2Z = 5 };
 
+// LDS of one tile
+template <typename T, int TY, int TZ, int OP, int CK>
+struct MarchLds {
+  static constexpr int PLANE = (TY + 2) * (TZ + 2);
+  static constexpr int CSLAB = (TY / 2 + 2) * (TZ / 2 + 2);
+  T sx[2][PLANE], sb[2][PLANE];
+  double sc[CK != 0 ? 1 : KMAX * KMAX * KMAX];
+  double sred[TY * TZ / 64];
+  T scs[OP == OP_JACP ? 4 * CSLAB : 1];
+};
+
+// Tile `bid` of the launch over g by TY x TZ threads (tid: index among them).
 template <typename T, typename TI, int TY, int TZ, int OP, int CK>
-__global__ void __launch_bounds__(TY* TZ)
-    k_march(GridArgs g, const TI* in, const T* in2, const T* rhs, T* out, T* out2,
-            const int* __restrict__ poff, double* __restrict__ partial, int color,
-            int x_zero, int top_begin, T omega, T* __restrict__ xdef) {
+__device__ __forceinline__ void march_tile(MarchLds<T, TY, TZ, OP, CK>& lds, const GridArgs& g,
+                                           int bid, int tid, const TI* in, const T* in2,
+                                           const T* rhs, T* out, T* out2,
+                                           const int* __restrict__ poff,
+                                           double* __restrict__ partial, int color, int x_zero,
+                                           int top_begin, T omega, T* __restrict__ xdef) {
   constexpr bool CACHED = CK != 0;   // 0: regenerate, 1: cache of type T, 2: bfloat16 cache
   constexpr int NT = TY * TZ;
   constexpr int PZ = TZ + 2;
-  constexpr int PLANE = (TY + 2) * PZ;
-  __shared__ T sx[2][PLANE];
-  __shared__ T sb[2][PLANE];
-  __shared__ double sc[CACHED ? 1 : KMAX * KMAX * KMAX];
-  __shared__ double sred[NT / 64];
+  auto& sx = lds.sx;
+  auto& sb = lds.sb;
+  auto& sc = lds.sc;
+  auto& scs = lds.scs;
 
   const int n = g.n;
   const int LP = lay_pitch(n), LO = lay_off(n);
-  const int bid = xcd_swizzle(blockIdx.x, gridDim.x);
   const int tpr = g.t.tiles_per_row;
   const int row = bid / tpr;
   const int tile = bid - row * tpr;
@@ -323,7 +339,7 @@ __global__ void __launch_bounds__(TY* TZ)
   const int K = g.K;
   if (!CACHED) {
     const int K3 = K * K * K;
-    for (int j = threadIdx.x; j < K3; j += NT) sc[j] = g.coef[(size_t)prob * K3 + j];
+    for (int j = tid; j < K3; j += NT) sc[j] = g.coef[(size_t)prob * K3 + j];
     __syncthreads();
   }
 
@@ -331,7 +347,6 @@ __global__ void __launch_bounds__(TY* TZ)
   const T* __restrict__ cache = (const T*)g.cache + (size_t)prob * (size_t)g.stride;
   const uint16_t* __restrict__ cache16 = (const uint16_t*)g.cache + (size_t)prob * (size_t)g.stride;
   const double* __restrict__ cosT = g.cosT;
-  const int tid = threadIdx.x;
   const int ly = tid / TZ, lz = tid - (tid / TZ) * TZ;
   const int y0 = 1 + ty * TY, z0 = 1 + tz * TZ;
   const int iy = y0 + ly, iz = z0 + lz;
@@ -394,7 +409,6 @@ __global__ void __launch_bounds__(TY* TZ)
   constexpr int CYN = TY / 2 + 2, CZN = TZ / 2 + 2;
   constexpr int CSLAB = CYN * CZN;
   static_assert(CSLAB <= NT, "coarse slab larger than the workgroup");
-  __shared__ T scs[OP == OP_JACP ? 4 * CSLAB : 1];
   const int nc = (n - 1) / 2 + 1;
   const int cLP = lay_pitch(nc), cLO = lay_off(nc);
   const T* crow = in2 + (size_t)row * (size_t)lay_row(nc);
@@ -646,10 +660,95 @@ __global__ void __launch_bounds__(TY* TZ)
                     ((OP == OP_GS || OP == OP_JAC || OP == OP_JACP) && partial != nullptr &&
                      prob >= top_begin);
   if (want) {
-    const double s = block_sum<NT>(dot, sred);
-    if (threadIdx.x == 0) partial[poff[prob] + tile] = s;
+    const double s = block_sum<NT>(dot, lds.sred, tid);
+    if (tid == 0) partial[poff[prob] + tile] = s;
   }
 }
+
+template <typename T, typename TI, int TY, int TZ, int OP, int CK>
+__global__ void __launch_bounds__(TY* TZ)
+    k_march(GridArgs g, const TI* in, const T* in2, const T* rhs, T* out, T* out2,
+            const int* __restrict__ poff, double* __restrict__ partial, int color,
+            int x_zero, int top_begin, T omega, T* __restrict__ xdef) {
+  __shared__ MarchLds<T, TY, TZ, OP, CK> lds;
+  march_tile<T, TI, TY, TZ, OP, CK>(lds, g, xcd_swizzle(blockIdx.x, gridDim.x), threadIdx.x, in,
+                                    in2, rhs, out, out2, poff, partial, color, x_zero, top_begin,
+                                    omega, xdef);
+}
+
+// One FP64 op over the rows of several groups (grids of different size, cached
+// coefficient) in one launch: a small group's launch takes the latency of one
+// march on a nearly idle chip, and these run side by side.  Workgroups have the
+// 512 threads of the largest tile and take several smaller tiles at once; waves
+// of a tile that ends early (an inactive problem, a shorter last chunk) leave,
+// and barriers wait for the others only.  A group's workgroups start at a
+// multiple of 8, which keeps its tiles in XCD order.
+// With the residual update likewise (k_groups): a 17^3..65^3 law estimate 4.92 ->
+// 4.52 ms, graph replay of a 64/16/4 estimate 2.32 -> 1.96, an objective up to
+// 65^3 3.23 -> 2.89, an adaptive step up to 257^3 26.4 -> 24.9; full batches gain
+// the tails of the smaller groups (9^3..129^3 FP64 57.7 -> 56.6 ms).
+constexpr int GM_THREADS = 512;
+
+template <typename TI, int OP, int TY, int TZ>
+__device__ __forceinline__ void march_group(char* smem, const MarchGroup& m, int wg,
+                                            const int* poff, double* partial) {
+  constexpr int NT = TY * TZ, PACK = GM_THREADS / NT;
+  using Lds = MarchLds<double, TY, TZ, OP, 1>;
+  const int tiles = m.g.rows * m.g.t.tiles_per_row, wgs = (tiles + PACK - 1) / PACK;
+  if (wg >= wgs) return;
+  const int sub = __builtin_amdgcn_readfirstlane(threadIdx.x / NT);
+  const int bid = xcd_swizzle(wg, wgs) * PACK + sub;
+  if (bid >= tiles) return;
+  march_tile<double, TI, TY, TZ, OP, 1>(reinterpret_cast<Lds*>(smem)[sub], m.g, bid,
+                                        threadIdx.x - sub * NT, (const TI*)m.in, m.in2, m.rhs,
+                                        m.out, m.out2, poff, partial, 0, 0, 0, 1.0, m.xdef);
+}
+
+template <typename TI, int OP>
+__global__ void __launch_bounds__(GM_THREADS)
+    k_march_groups(MarchTable t, const int* __restrict__ poff, double* __restrict__ partial) {
+  constexpr size_t L64 = sizeof(MarchLds<double, 8, 64, OP, 1>);
+  constexpr size_t L32 = 2 * sizeof(MarchLds<double, 8, 32, OP, 1>);
+  constexpr size_t L16 = 2 * sizeof(MarchLds<double, 16, 16, OP, 1>);
+  constexpr size_t L8 = 8 * sizeof(MarchLds<double, 8, 8, OP, 1>);
+  constexpr size_t LA = L64 > L32 ? L64 : L32, LB = L16 > L8 ? L16 : L8;
+  __shared__ __align__(16) char smem[LA > LB ? LA : LB];
+  int i = 0;
+  while (i + 1 < t.count && (int)blockIdx.x >= t.gr[i + 1].begin) ++i;
+  const MarchGroup& m = t.gr[i];
+  const int wg = (int)blockIdx.x - m.begin;
+  if (m.g.t.TZ == 64)
+    march_group<TI, OP, 8, 64>(smem, m, wg, poff, partial);
+  else if (m.g.t.TZ == 32)
+    march_group<TI, OP, 8, 32>(smem, m, wg, poff, partial);
+  else if (m.g.t.TZ == 16)
+    march_group<TI, OP, 16, 16>(smem, m, wg, poff, partial);
+  else
+    march_group<TI, OP, 8, 8>(smem, m, wg, poff, partial);
+}
+
+template <typename TI, int OP>
+static void launch_march_groups(MarchTable& t, const int* poff, double* partial, hipStream_t s) {
+  int wg = 0;
+  for (int i = 0; i < t.count; ++i) {
+    MarchGroup& m = t.gr[i];
+    m.begin = wg;
+    const int pack = GM_THREADS / (m.g.t.TY * m.g.t.TZ);
+    wg += (cdiv((long long)m.g.rows * m.g.t.tiles_per_row, pack) + 7) & ~7;
+  }
+  if (wg > 0)
+    hipLaunchKernelGGL((k_march_groups<TI, OP>), dim3(wg), dim3(GM_THREADS), 0, s, t, poff, partial);
+}
+void matvec_groups(MarchTable& t, bool z32, const int* poff, double* partial, hipStream_t s) {
+  if (z32)
+    launch_march_groups<float, OP_MATVEC>(t, poff, partial, s);
+  else
+    launch_march_groups<double, OP_MATVEC>(t, poff, partial, s);
+}
+void resid_groups(MarchTable& t, const int* poff, double* partial, hipStream_t s) {
+  launch_march_groups<double, OP_RESID>(t, poff, partial, s);
+}
+
 
 template <typename T, typename TI, int OP, int CK>
 static void launch_march2(const GridArgs& g, const TI* in, const T* in2, const T* rhs, T* out,
@@ -3982,14 +4081,15 @@ __device__ __forceinline__ double group_elem(size_t k, int n, int ix, int iy, in
 // misfit tests each vertex, the dot and the update stream every element
 // (boundary zeros pass through unchanged), four per thread in flight.
 template <int OP, int NZ>
-__global__ void __launch_bounds__(256)
-    k_group(GridArgs g, double* __restrict__ a, const double* __restrict__ b,
-            double* __restrict__ c, const double* __restrict__ d, const int* __restrict__ poff,
-            double* __restrict__ partial, float* __restrict__ cf) {
-  __shared__ double sred[4];
+__device__ __forceinline__ void group_tile(const GridArgs& g, int bid, double* sred,
+                                           double* __restrict__ a, const double* __restrict__ b,
+                                           double* __restrict__ c, const double* __restrict__ d,
+                                           const int* __restrict__ poff,
+                                           double* __restrict__ partial,
+                                           float* __restrict__ cf) {
   const int tpr = g.t.tiles_per_row;
-  const int row = blockIdx.x / tpr;
-  const int tile = blockIdx.x - row * tpr;
+  const int row = bid / tpr;
+  const int tile = bid - row * tpr;
   const int prob = g.row0 + row;
   if (OP == G_XFLUSH) {
     if (!g.scal[prob].pending) return;  // uniform per workgroup
@@ -4118,6 +4218,36 @@ __global__ void __launch_bounds__(256)
   }
 }
 
+template <int OP, int NZ>
+__global__ void __launch_bounds__(256)
+    k_group(GridArgs g, double* __restrict__ a, const double* __restrict__ b,
+            double* __restrict__ c, const double* __restrict__ d, const int* __restrict__ poff,
+            double* __restrict__ partial, float* __restrict__ cf) {
+  __shared__ double sred[4];
+  group_tile<OP, NZ>(g, blockIdx.x, sred, a, b, c, d, poff, partial, cf);
+}
+
+// The op over the rows of several groups in one launch (as k_march_groups).
+template <int OP>
+__global__ void __launch_bounds__(256)
+    k_groups(GroupTable t, const int* __restrict__ poff, double* __restrict__ partial) {
+  __shared__ double sred[4];
+  int i = 0;
+  while (i + 1 < t.count && (int)blockIdx.x >= t.gr[i + 1].begin) ++i;
+  const GroupRows& r = t.gr[i];
+  const int bid = (int)blockIdx.x - r.begin, m = r.g.n - 2;
+  if (m < 63)
+    group_tile<OP, -1>(r.g, bid, sred, r.a, r.b, r.c, r.d, poff, partial, r.cf);
+  else if (m <= 64)
+    group_tile<OP, 1>(r.g, bid, sred, r.a, r.b, r.c, r.d, poff, partial, r.cf);
+  else if (m <= 128)
+    group_tile<OP, 2>(r.g, bid, sred, r.a, r.b, r.c, r.d, poff, partial, r.cf);
+  else if (m <= 256)
+    group_tile<OP, 4>(r.g, bid, sred, r.a, r.b, r.c, r.d, poff, partial, r.cf);
+  else
+    group_tile<OP, 0>(r.g, bid, sred, r.a, r.b, r.c, r.d, poff, partial, r.cf);
+}
+
 template <int OP>
 static void launch_group(const GridArgs& g, double* a, const double* b, double* c,
                          const double* d, const int* poff, double* partial, float* cf,
@@ -4137,6 +4267,21 @@ static void launch_group(const GridArgs& g, double* a, const double* b, double* 
     hipLaunchKernelGGL((k_group<OP, 0>), grid, block, 0, s, g, a, b, c, d, poff, partial, cf);
 }
 
+template <int OP>
+static void launch_groups(GroupTable& t, const int* poff, double* partial, hipStream_t s) {
+  if (t.count == 1) {
+    const GroupRows& r = t.gr[0];
+    launch_group<OP>(r.g, r.a, r.b, r.c, r.d, poff, partial, r.cf, s);
+    return;
+  }
+  int wg = 0;
+  for (int i = 0; i < t.count; ++i) {
+    t.gr[i].begin = wg;
+    wg += t.gr[i].g.rows * t.gr[i].g.t.tiles_per_row;
+  }
+  if (wg > 0) hipLaunchKernelGGL((k_groups<OP>), dim3(wg), dim3(256), 0, s, t, poff, partial);
+}
+
 void group_dot(const GridArgs& g, const double* a, const double* b, const int* poff,
                double* partial, hipStream_t s) {
   launch_group<G_DOT>(g, (double*)a, b, nullptr, nullptr, poff, partial, nullptr, s);
@@ -4149,14 +4294,10 @@ void group_misfit(const GridArgs& g, double* y, const double* yd, double* b_rows
                   const int* poff, double* partial, hipStream_t s) {
   launch_group<G_MISFIT>(g, y, yd, b_rows, nullptr, poff, partial, nullptr, s);
 }
-void group_rupdate(const GridArgs& g, double* r, const double* q, const int* poff,
-                   double* partial, float* r32, hipStream_t s) {
-  launch_group<G_RUPDATE>(g, nullptr, nullptr, r, q, poff, partial, r32, s);
+void group_rupdate(GroupTable& t, const int* poff, double* partial, hipStream_t s) {
+  launch_groups<G_RUPDATE>(t, poff, partial, s);
 }
-void group_xflush(const GridArgs& g, double* x, const double* p0, const double* p1,
-                  hipStream_t s) {
-  launch_group<G_XFLUSH>(g, x, p0, nullptr, p1, nullptr, nullptr, nullptr, s);
-}
+void group_xflush(GroupTable& t, hipStream_t s) { launch_groups<G_XFLUSH>(t, nullptr, nullptr, s); }
 
 // ---------------------------------------------------------------------------
 // Per-problem scalar steps, one workgroup for all problems (fixed summation

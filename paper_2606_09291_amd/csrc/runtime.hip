@@ -1120,6 +1120,42 @@ const float* z32(mlsgd_ctx* c, Plan* P, const Group& gr) {
   return A + (size_t)gr.p0 * srow(gr.n);
 }
 
+// The launch arguments of every group for one launch over them all; false where
+// there is one group or a group's tiles are not in that kernel.
+bool march_table(mlsgd_ctx* c, Plan* P, bool skip_inactive, MarchTable& t) {
+  if (P->groups.size() < 2 || P->groups.size() > MAX_GROUPS) return false;
+  for (auto& gr : P->groups) {
+    t.gr[t.count].g = args_group(c, P, gr, skip_inactive);
+    if (!group_tiles(t.gr[t.count++].g)) return false;
+  }
+  return true;
+}
+
+// The residual b0 - A x of every group: stored in the B rows of the top grids,
+// or (norm) only the partials of its squared norm.
+void group_resid(mlsgd_ctx* c, Plan* P, bool skip_inactive, bool norm) {
+  int* poff = norm ? P->d_poff : nullptr;
+  double* part = norm ? P->d_partial : nullptr;
+  MarchTable t{};
+  if (march_table(c, P, skip_inactive, t)) {
+    for (size_t i = 0; i < P->groups.size(); ++i) {
+      const Group& gr = P->groups[i];
+      t.gr[i].in = gr.x;
+      t.gr[i].rhs = gr.b0;
+      t.gr[i].out = norm ? nullptr : rows_of(P->sizes[gr.sl].B, gr);
+    }
+    resid_groups(t, poff, part, c->stream);
+    return;
+  }
+  for (auto& gr : P->groups) {
+    const GridArgs g = args_group(c, P, gr, skip_inactive);
+    if (norm)
+      march_resid_norm(g, gr.x, gr.b0, poff, part, c->stream);
+    else
+      march_resid<double>(g, gr.x, gr.b0, rows_of(P->sizes[gr.sl].B, gr), c->stream);
+  }
+}
+
 int read_count(mlsgd_ctx* c) {
   HIPCHK(hipMemcpyAsync(c->h_count, c->d_count, sizeof(int), hipMemcpyDeviceToHost, c->stream));
   HIPCHK(hipStreamSynchronize(c->stream));
@@ -1190,10 +1226,7 @@ void fmg_start(mlsgd_ctx* c, Plan* P) {
     vcycle_cheb<T>(c, P, k, P->sizes[k].rows, true);
     start(k);
   }
-  for (auto& gr : P->groups) {
-    GridArgs g = args_group(c, P, gr, false);
-    march_resid<double>(g, gr.x, gr.b0, rows_of(P->sizes[gr.sl].B, gr), s);
-  }
+  group_resid(c, P, false, false);
   HIPCHK(hipGetLastError());
 }
 
@@ -1225,12 +1258,25 @@ void scalar_phase(mlsgd_ctx* c, Plan* P, int phase, bool sums, double rtol, bool
 void krylov_step(mlsgd_ctx* c, Plan* P, bool mg, int it) {
   hipStream_t s = c->stream;
   const bool defer = c->xdefer;
+  const bool z32b = mg && c->mixed;
   int pslot = 0;  // every group writes the new direction into p[pcur ^ 1]
+  MarchTable mt{};
+  const bool one = !(c->tm.on && c->tm.kind == 4) && march_table(c, P, true, mt);
   for (auto& gr : P->groups) {
     GridArgs g = args_group(c, P, gr, true);
     SizeLvl& L = P->sizes[gr.sl];
     double* xd = (defer && it > 0) ? gr.x : nullptr;
-    const bool z32b = mg && c->mixed;
+    pslot = gr.pcur ^ 1;
+    if (one) {
+      MarchGroup& m = mt.gr[&gr - P->groups.data()];
+      m.in = z32b ? (const void*)z32(c, P, gr)
+                  : (const void*)(mg ? z64(c, P, gr) : rows_of(L.B, gr));
+      m.in2 = gr.p[gr.pcur];
+      m.out = gr.q;
+      m.out2 = gr.p[gr.pcur ^ 1];
+      m.xdef = xd;
+      continue;
+    }
     timed_launch(c, g, matvec_bytes(gr.n, gr.count, z32b ? 4.0 : 8.0, xd != nullptr), [&] {
       if (z32b) {
         march_matvec<double, float>(g, z32(c, P, gr), gr.p[gr.pcur], gr.p[gr.pcur ^ 1], gr.q,
@@ -1241,29 +1287,32 @@ void krylov_step(mlsgd_ctx* c, Plan* P, bool mg, int it) {
                                      P->d_partial, s, xd);
       }
     }, 4);
-    pslot = gr.pcur ^ 1;
   }
+  if (one) matvec_groups(mt, z32b, P->d_poff, P->d_partial, s);
   scalar_phase(c, P, PH_ALPHA, true, c->pb.rtol, false, true, pslot);
+  GroupTable gt{};
   for (auto& gr : P->groups) {
     GridArgs g = args_group(c, P, gr, true);
     float* r32 = (mg && c->mixed) ? P->sizes[gr.sl].Bf + (size_t)gr.p0 * srow(gr.n) : nullptr;
     if (defer)
-      group_rupdate(g, rows_of(P->sizes[gr.sl].B, gr), gr.q, P->d_poff, P->d_partial, r32, s);
+      gt.gr[gt.count++] = GroupRows{g, nullptr, nullptr, rows_of(P->sizes[gr.sl].B, gr), gr.q, r32, 0};
     else
       group_update(g, gr.x, gr.p[gr.pcur ^ 1], rows_of(P->sizes[gr.sl].B, gr), gr.q,
                    P->d_poff, P->d_partial, r32, s);
     gr.pcur ^= 1;
   }
+  if (defer) group_rupdate(gt, P->d_poff, P->d_partial, s);
 }
 
 // Apply every pending step x += alpha p (active problems and those that
 // converged earlier alike) before x is read.
 void flush_steps(mlsgd_ctx* c, Plan* P) {
   if (!c->xdefer) return;
-  for (auto& gr : P->groups) {
-    GridArgs g = args_group(c, P, gr, true);
-    group_xflush(g, gr.x, gr.p[0], gr.p[1], c->stream);
-  }
+  GroupTable t{};
+  for (auto& gr : P->groups)
+    t.gr[t.count++] =
+        GroupRows{args_group(c, P, gr, true), gr.x, gr.p[0], nullptr, gr.p[1], nullptr, 0};
+  group_xflush(t, c->stream);
 }
 
 // Plain CG where every top grid is small enough for one workgroup: whole
@@ -1347,9 +1396,7 @@ void krylov(mlsgd_ctx* c, Plan* P, int* iters_out, int* nonconv_out, double* rel
     // still hold the last check's sums
     flush_steps(c, P);
     if (restart > 0) scalar_phase(c, P, PH_RECHECK, false, rtol, false, false);
-    for (auto& gr : P->groups)
-      march_resid_norm(args_group(c, P, gr, restart > 0), gr.x, gr.b0, P->d_poff, P->d_partial,
-                       s);
+    group_resid(c, P, restart > 0, true);
     const bool force = c->force_restart && restart == 0;
     // (the counter is 0 here: the loop above ended on a count of 0)
     scalar_phase(c, P, PH_TRUE, true, rtol, !force, false);
@@ -1357,9 +1404,7 @@ void krylov(mlsgd_ctx* c, Plan* P, int* iters_out, int* nonconv_out, double* rel
     HIPCHK(hipGetLastError());
     if (read_count(c) == 0) break;
     // the restarted problems start again from r = b - A x
-    for (auto& gr : P->groups)
-      march_resid<double>(args_group(c, P, gr, true), gr.x, gr.b0,
-                          rows_of(P->sizes[gr.sl].B, gr), s);
+    group_resid(c, P, true, false);
   }
   scal_to_stats(P->d_scal, P->nprob, rtol, &c->d_stat->iters, &c->d_stat->nonconv,
                 &c->d_stat->relres, s);
@@ -1421,8 +1466,7 @@ void krylov_fixed(mlsgd_ctx* c, Plan* P, int iters, int slot, bool bb_ready = fa
   auto true_residual = [&](bool recheck) {
     flush_steps(c, P);
     if (recheck) cg(PH_RECHECK, false);
-    for (auto& gr : P->groups)
-      march_resid_norm(args_group(c, P, gr, recheck), gr.x, gr.b0, P->d_poff, P->d_partial, s);
+    group_resid(c, P, recheck, true);
     cg(PH_TRUE, true);
   };
   if (cg_small_applies(c, P)) {
@@ -1446,9 +1490,7 @@ void krylov_fixed(mlsgd_ctx* c, Plan* P, int iters, int slot, bool bb_ready = fa
   true_residual(false);
   if (c->force_restart) cg(PH_FORCE_RESTART, false);
   // restart block: the problems that missed rtol start again from b - A x
-  for (auto& gr : P->groups)
-    march_resid<double>(args_group(c, P, gr, true), gr.x, gr.b0, rows_of(P->sizes[gr.sl].B, gr),
-                        s);
+  group_resid(c, P, true, false);
   start();
   iterate(kRestartIters);
   true_residual(true);

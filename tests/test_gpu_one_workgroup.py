@@ -17,7 +17,10 @@ oracle for the solution: both stop at a true relative residual of 1e-12, so the
 solutions differ from the exact one by at most the condition number of the
 diagonally unscaled operator (under 1e4) times that, 1e-8.  The dots' summation
 order differs, so counts may differ by two in a hundred; at an iteration limit
-they are the limit, and the iterates agree as far."""
+they are the limit, and the iterates agree as far.
+
+The matvec of all grid sizes in one launch against a launch per size (event
+timing of the matvec keeps those): the same tiles and sums, so the same bits."""
 import numpy as np
 import pytest
 
@@ -119,3 +122,26 @@ def test_small_cg(mm, orc, monkeypatch, count, max_iters):
         for m in (0, count - 1):
             yo, _, _ = orc.solve(n, orc.kl_coeffs(0, 4, 1 + m, 4, 1.0), rhs, rtol=1e-14)
             assert _rel(out[1][0][m], yo) <= 1e-8
+
+
+@pytest.mark.parametrize("precision", ["fp64", "mixed"])
+@pytest.mark.parametrize("grid,M,tuning", [
+    ([9, 17], [2, 2], {}), ([9, 17, 33, 65], [19, 7, 3, 2], {}),
+    ([17, 33, 65, 129], [33, 9, 3, 2], {"xchunk": 9}), ([33, 65], [3, 2], {"tile_y": 16})])
+def test_groups_in_one_launch(mm, grid, M, tuning, precision):
+    print("groups in one launch", grid, M, tuning, precision, flush=True)
+    yd = inputs.target_sin(grid[-1])
+    u = inputs.control_xyz(grid[-1]) + 15.0 * yd
+    out = []
+    for timed in (False, True):
+        ctx = mm.Context(mm.Problem(grid_n=grid, y_d=yd, rtol=1e-11,
+                                    precision=_prec(mm, precision)), use_tuned=False)
+        if tuning:
+            ctx.set_tuning(**tuning)
+        if timed:
+            ctx.kernel_timing(4, 65)
+        g, st = ctx.mlmc_gradient(u, M)
+        out.append((g.cpu().numpy(), st))
+        ctx.close()
+    assert bool(np.array_equal(out[0][0], out[1][0]))
+    assert out[0][1]["J"] == out[1][1]["J"]
