@@ -145,7 +145,7 @@ static inline int cdiv(long long a, long long b) { return (int)((a + b - 1) / b)
 
 // A workgroup marches its chunk at about a memory round trip per plane, so a
 // batch too small to fill the chip takes as long as one chunk.  With the batch's
-// rows known, the chunk is halved (to even lengths >= 4) while that shortens the
+// rows known, the chunk is halved (to even lengths) while that shortens the
 // estimate rounds x (planes + 6): rounds of the workgroups that fit at once, the
 // chunk's planes, and about six planes' worth of first loads and ring planes.  A
 // gain under 15% keeps the longer chunk (each chunk repeats two ring planes),
@@ -153,6 +153,8 @@ static inline int cdiv(long long a, long long b) { return (int)((a + b - 1) / b)
 // Measured, 32-plane chunks against the rule: one 33^3 state and adjoint solve 4.1
 // -> 2.0 ms (post-smoothing 48 -> 14 us a pass), the 17^3..65^3 law workload 13.8
 // -> 6.5, 300 solves of 33^3..65^3 26.7 -> 23.7; full batches keep their chunks.
+// Two planes against four as the shortest chunk: one 33^3 state and adjoint solve
+// 1.45 -> 1.29 ms, graph replay of a 64/16/4 estimate 1.97 -> 1.87.
 static int split_chunk(const Tiling& t, int m, int rows) {
   const int threads = t.TY * t.TZ;
   const long long fit = 256LL * (threads >= 1024 ? 1 : 1024 / threads);
@@ -164,7 +166,6 @@ static int split_chunk(const Tiling& t, int m, int rows) {
   // one chunk of an odd number of planes splits as the even length above it
   for (int ch = (t.nxc == 1 ? t.xchunk + (t.xchunk & 1) : t.xchunk); ch % 4 == 0;) {
     ch /= 2;
-    if (ch < 4) break;
     if (100 * cost(ch) < 85 * cost(best)) best = ch;
   }
   return best;
@@ -1545,7 +1546,7 @@ VTile make_vtile(int n, int elem, int tile_y, int xchunk, int rows) {
     best = m;
     for (;; ch /= 2) {
       if (ch < m && cost(ch) < cost(best)) best = ch;
-      if (ch % 4 || ch / 2 < 4) break;
+      if (ch % 4) break;
     }
   }
   v.xchunk = best;
