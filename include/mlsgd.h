@@ -293,7 +293,9 @@ typedef struct mlsgd_tuning {
   double omega;       /* red-black relaxation weight, (0, 2) */
   double cheb_lo;     /* lower end of the Chebyshev interval as a fraction of 2, (0, 1) */
   int32_t tile_y;     /* y extent of the stencil tiles on grids with > 32 interior points: 4, 8, 16 */
-  int32_t xchunk;     /* x planes marched by one workgroup, 8..1024 */
+  int32_t xchunk;     /* x planes marched by one workgroup, 8..1024.  A batch that leaves the
+                       * chip idle takes fewer; the fused smoothing passes on lines of up to 64
+                       * 16-byte vectors choose their own rows and a chunk from it by the batch */
   int32_t cache;      /* 1: coefficient regenerated once per call into a cache; 0: in every sweep */
 } mlsgd_tuning;
 

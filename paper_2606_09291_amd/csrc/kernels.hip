@@ -3347,7 +3347,7 @@ __global__ void k_restrict_rows(int nf, int rows, int row0, const CgScal* scal,
   }
 }
 
-// The y and z parts of full weighting after k_pre2r's x part: coarse vertex
+// The y and z parts of full weighting after the pre-smoothing pass's x part: coarse vertex
 // (I, J, K) = sum over dy of w(dy) (h(I, 2J+dy, 2K-1) / 4 + h(I, 2J+dy, 2K) / 2
 // + h(I, 2J+dy, 2K+1) / 4), w = 1/2 at dy = 0 and 1/4 at dy = +-1, with h
 // plane I held in plane I of the fine row.

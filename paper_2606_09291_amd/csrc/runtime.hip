@@ -1120,6 +1120,7 @@ const float* z32(mlsgd_ctx* c, Plan* P, const Group& gr) {
   return A + (size_t)gr.p0 * srow(gr.n);
 }
 
+static_assert(MAX_GROUPS >= MLSGD_MAX_LEVELS, "a group per level");
 // The launch arguments of every group for one launch over them all; false where
 // there is one group or a group's tiles are not in that kernel.
 bool march_table(mlsgd_ctx* c, Plan* P, bool skip_inactive, MarchTable& t) {
