@@ -142,10 +142,10 @@ def run(args, m, w, dev, steps, warmup, timing_n=None, graph=False, timing_kind=
 
 
 KERNEL_NAMES = {
-    2: ("fused post-smoothing pass (k_post2: coarse-grid correction folded in, two Chebyshev "
+    2: ("fused post-smoothing pass (k_post2v, k_post2: coarse-grid correction folded in, two Chebyshev "
         "steps, cached 1/a) on the {n}^3 rows"),
     1: "Chebyshev smoothing step (k_march OP_JAC, damped Jacobi, cached 1/a) on the {n}^3 rows",
-    3: ("fused pre-smoothing pass (k_pre2r: two Chebyshev steps from zero, residual restricted "
+    3: ("fused pre-smoothing pass (k_pre2v, k_pre2r: two Chebyshev steps from zero, residual restricted "
         "along x, cached 1/a and 1/D) on the {n}^3 rows"),
     4: ("Krylov matvec (k_march OP_MATVEC: p = z + beta p, q = A p, deferred x step, cached 1/a) "
         "on the {n}^3 rows"),
