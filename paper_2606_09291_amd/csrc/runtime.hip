@@ -115,7 +115,8 @@ struct Plan {
   CgScal* d_scal = nullptr;
   int* d_poff = nullptr;
   int* d_pcnt = nullptr;
-  int* d_vcnt = nullptr;
+  int* d_vcnt = nullptr;   // d_pcnt itself where no count differs
+  bool vcnt_own = false;
   double* d_partial = nullptr;
   double* d_phi = nullptr;
   double* d_w = nullptr;
@@ -382,6 +383,7 @@ void plan_layout(mlsgd_ctx* c, const std::vector<Block>& blocks, Plan* P, bool s
   for (const auto& g : P->groups) {
     const SizeLvl& L = P->sizes[g.sl];
     const int slots = std::max(L.t.tiles_per_row, L.vslots);
+    P->vcnt_own |= L.vslots != L.t.tiles_per_row;
     P->max_slots = std::max(P->max_slots, slots);
     for (int q = g.p0; q < g.p0 + g.count; ++q, off += slots) {
       P->h_pcnt[q] = L.t.tiles_per_row;
@@ -430,7 +432,9 @@ size_t plan_carve(mlsgd_ctx* c, Plan* P, char* base) {
   P->d_scal = cv.take<CgScal>(np);
   P->d_poff = cv.take<int>(np);
   P->d_pcnt = cv.take<int>(np);
-  P->d_vcnt = cv.take<int>(np);
+  // (the largest batches of the allocation-free entry, of 5^3 and 9^3 grids, have
+  // no room for a second list)
+  P->d_vcnt = P->vcnt_own ? cv.take<int>(np) : P->d_pcnt;
   P->d_partial = cv.take<double>((size_t)P->npartial);
   P->d_phi = cv.take<double>(np);
   P->d_w = cv.take<double>(np);
@@ -451,8 +455,9 @@ void plan_init(mlsgd_ctx* c, Plan* P) {
                         hipMemcpyHostToDevice, c->stream));
   HIPCHK(hipMemcpyAsync(P->d_pcnt, P->h_pcnt.data(), sizeof(int) * P->nprob,
                         hipMemcpyHostToDevice, c->stream));
-  HIPCHK(hipMemcpyAsync(P->d_vcnt, P->h_vcnt.data(), sizeof(int) * P->nprob,
-                        hipMemcpyHostToDevice, c->stream));
+  if (P->vcnt_own)
+    HIPCHK(hipMemcpyAsync(P->d_vcnt, P->h_vcnt.data(), sizeof(int) * P->nprob,
+                          hipMemcpyHostToDevice, c->stream));
 }
 
 // Upload the (level, sample) keys of this call's draws; `fields` also
