@@ -171,6 +171,9 @@ static int split_chunk(const Tiling& t, int m, int rows) {
   return best;
 }
 
+// x planes of a chunk as asked for; lengths below 8 stand for the default
+static int chunk_planes(int xchunk) { return xchunk >= 8 ? xchunk : 32; }
+
 Tiling make_tiling(int n, int tile_y, int xchunk, int rows) {
   const int m = n - 2;
   Tiling t;
@@ -184,7 +187,7 @@ Tiling make_tiling(int n, int tile_y, int xchunk, int rows) {
     t.TY = (tile_y == 4 || tile_y == 16) ? tile_y : 8;
     t.TZ = 64;
   }
-  const int xch = xchunk >= 8 ? xchunk : 32;
+  const int xch = chunk_planes(xchunk);
   t.nty = cdiv(m, t.TY);
   t.ntz = cdiv(m, t.TZ);
   t.xchunk = m <= xch ? m : xch;
@@ -1515,6 +1518,7 @@ struct VecOf {
 VTile make_vtile(int n, int elem, int tile_y, int xchunk, int rows) {
   VTile v{};
   const int V = 16 / elem, m = n - 2;
+  xchunk = chunk_planes(xchunk);
   // lines that are no whole number of vectors (11 and 15 vertices in FP32) or
   // longer than 64 of them, 9^3 and below (k_vsmall) and the 4 x 64 tiles
   // (which keep the separate passes) have no vector form
