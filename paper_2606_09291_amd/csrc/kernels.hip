@@ -2505,6 +2505,10 @@ __global__ void __launch_bounds__(64 * VS_WAVES)
 // that come first: they are the shorter ones, and the CUs they free take the
 // 17^3 problems that did not fit at once (an objective with 231 and 932 problems
 // on 17^3 and 9^3 2.89 -> 2.83 ms against the other order).
+// Faces and reciprocal diagonals take the two-step reciprocal: the first step of
+// a pre-smoothing pass (k_dinv) and the residual after the start's have it too.  The
+// one-step form would leave up to 2.1e-15 in them (at most 1.1e-16 with two); it
+// measured 1.324 against 1.348 ms on one 33^3 state and adjoint solve.
 // Two register sets (the 17^3 waves' 130 and the ninth's 200) share 168 VGPRs a
 // lane; the compiler keeps some thirty of the ninth wave's values in scratch.
 // Gradients on one level of 17^3, 64 / 256 / 512 samples: FP64 1.31 -> 1.07,
@@ -2592,16 +2596,16 @@ __global__ void __launch_bounds__(64 * VM_WAVES)
     // (planes beyond the grid stand for points that are not owned)
     auto bp = [&](int j) { return &v17[1][l0 + (x0 + j <= 16 ? j : 16 - x0) * VM_PP]; };
 #pragma unroll
-    for (int j = 0; j <= VM_XS; ++j) fx[j] = sface(*bp(j - 1), *bp(j));
+    for (int j = 0; j <= VM_XS; ++j) fx[j] = face(*bp(j - 1), *bp(j));
 #pragma unroll
     for (int j = 0; j < VM_XS; ++j) {
       const T* p = bp(j);
-      fym[j] = sface(p[0], p[-VM_P]);
+      fym[j] = face(p[0], p[-VM_P]);
       // (the last plane's row past the grid is the boundary row itself)
-      fyp[j] = sface(p[0], p[VM_P]);
-      fzp[j] = sface(p[0], p[1]);
+      fyp[j] = face(p[0], p[VM_P]);
+      fzp[j] = face(p[0], p[1]);
       fzm[j] = __shfl_up(fzp[j], 1, 16);   // of lane iz - 1
-      di[j] = srcp(ih2 * (((fx[j] + fx[j + 1]) + (fym[j] + fyp[j])) + (fzm[j] + fzp[j])));
+      di[j] = drcp(ih2 * (((fx[j] + fx[j + 1]) + (fym[j] + fyp[j])) + (fzm[j] + fzp[j])));
     }
   }
   __syncthreads();   // faces formed
