@@ -196,7 +196,9 @@ struct MidArgs {
   const void *c17, *c9, *c5, *c3;
   T *x17, *x9;
 };
-constexpr int VM_ROWS = 1024;   // most rows17 it is used for
+// whether it is used for rows17 problems on 17^3 and tops9 with their top on 9^3
+// (elem: bytes of a value)
+bool mid_rows(int rows17, int tops9, int elem);
 template <typename T>
 void vcycle_mid(const double* om, int deg, int top9, const CgScal* scal, const MidArgs<T>& ma,
                 int cache_bf16, const int* poff, double* partial, bool start, hipStream_t s);

@@ -2717,6 +2717,23 @@ __global__ void __launch_bounds__(64 * VM_WAVES)
   }
 }
 
+// A workgroup of k_vmid fills a CU, so its time grows by a round for every 256 of
+// them (a 17^3 problem each, nine 9^3 problems each), where the separate passes
+// fill the chip better and better; k_vsmall holds some twenty 9^3 problems a CU.
+// FP64, gradients on 17^3 alone, separate against one kernel: 1024 samples 3.93 /
+// 3.75 ms, 1536 5.61 / 5.90.  With problems topped on 9^3 (levels 9^3 and 17^3,
+// M9 / M17) a first round always pays and a second only if 17^3 fills half of the
+// first: 2000 / 2 1.89 / 1.73, 2300 / 2 (258 workgroups) 2.18 / 2.21, 3000 / 32
+// 2.38 / 2.50, 3000 / 128 (476) 2.78 / 2.73, 3600 / 128 (543) 2.92 / 3.14, 1024 / 512
+// (683) 3.18 / 3.23, 16384 / 64 7.98 / 9.82.  FP32 cycles gain up to four rounds:
+// 8000 / 2 (891) 3.49 / 3.45, 6000 / 256 (951) 3.70 / 3.54, 4096 / 512 (1024) 3.85 /
+// 3.69, 10000 / 512 (1681) 5.90 / 6.33, 17^3 alone 1024 3.39 / 3.20, 1536 5.15 / 5.23.
+bool mid_rows(int rows17, int tops9, int elem) {
+  const int packs = cdiv(tops9, VM_WAVES);
+  if (elem == 4 || packs == 0) return rows17 + packs <= 1024;
+  return rows17 + packs <= 256 || (rows17 >= 128 && rows17 + packs <= 512);
+}
+
 template <typename T>
 void vcycle_mid(const double* om, int deg, int top9, const CgScal* scal, const MidArgs<T>& ma,
                 int cache_bf16, const int* poff, double* partial, bool start, hipStream_t s) {

@@ -784,18 +784,14 @@ bool small_cycle(mlsgd_ctx* c, Plan* P) {
   return true;
 }
 
-// The one-kernel cycle from 17^3 down applies, above it, to few problems: a
-// workgroup of it fills a CU, so its time grows by a round for every 256 rows
-// of 17^3, where the separate passes fill the chip better and better.  Both
-// meet between 1024 and 1536 rows (gradients on one level of 17^3, separate
-// against one kernel: 1024 samples 3.93 / 3.75 ms, 1536 5.61 / 5.90; FP32 cycles
-// 3.39 / 3.20, 5.15 / 5.23).  Event timing of the passes on 17^3 keeps them.
+// The one-kernel cycle from 17^3 down applies, above it, to few problems
+// (mid_rows).  Event timing of the passes on 17^3 keeps them.
 template <typename T>
 bool mid_cycle(mlsgd_ctx* c, Plan* P) {
   const int S = (int)P->sizes.size();
   if (S < 4 || (c->tm.on && c->tm.n == 17) || !small_cycle<T>(c, P)) return false;
   const SizeLvl& L = P->sizes[S - 4];
-  return L.n == 17 && L.rows <= VM_ROWS &&
+  return L.n == 17 && mid_rows(L.rows, P->sizes[S - 3].rows - L.rows, sizeof(T)) &&
          (sizeof(T) == 8 ? args_size(c, P, L) : args_size32(c, P, L)).cache;
 }
 
