@@ -323,9 +323,13 @@ int mlsgd_set_graph(mlsgd_ctx* ctx, int enable);
  * smoothing step (enable = 1), the fused two-step post-smoothing pass
  * (enable = 2), the fused pre-smoothing pass with its residual (enable = 3)
  * or the Krylov matvec (enable = 4); the fused passes run on grids with
- * 64-wide tiles of height 8 or 16 and a cached coefficient.  While a grid of
- * at most 17 vertices is timed, its passes run one by one where one kernel
- * would do their work together (results then differ by rounding).  The call
+ * 64-wide tiles of height 8 or 16 and a cached coefficient.  Timing keeps, on
+ * the timed grid, passes that one kernel would otherwise do together, so what
+ * it times there is no part of an untimed call and results differ from one's by
+ * rounding: the smoothing passes of 17^3 (enable = 1, 2, 3), the plain steps of
+ * the full-multigrid start on 9^3, 5^3 and 3^3 (enable = 1; the cycles there
+ * stay one kernel and are not timed), and the matvec of unpreconditioned CG up
+ * to 17^3 (enable = 4).  On every other grid results stay the same bits.  The call
  * first returns the totals accumulated so far (host outputs, nullable:
  * summed milliseconds, launch count, algorithmic bytes = interior points x
  * bytes the kernel must move, the coefficient counted at 0 bytes since the

@@ -785,11 +785,12 @@ bool small_cycle(mlsgd_ctx* c, Plan* P) {
 }
 
 // The one-kernel cycle from 17^3 down applies, above it, to few problems
-// (mid_rows).  Event timing of the passes on 17^3 keeps them.
+// (mid_rows).  Event timing of the smoothing passes on 17^3 keeps them.
 template <typename T>
 bool mid_cycle(mlsgd_ctx* c, Plan* P) {
   const int S = (int)P->sizes.size();
-  if (S < 4 || (c->tm.on && c->tm.n == 17) || !small_cycle<T>(c, P)) return false;
+  if (S < 4 || (c->tm.on && c->tm.kind != 4 && c->tm.n == 17) || !small_cycle<T>(c, P))
+    return false;
   const SizeLvl& L = P->sizes[S - 4];
   return L.n == 17 && mid_rows(L.rows, P->sizes[S - 3].rows - L.rows, sizeof(T)) &&
          (sizeof(T) == 8 ? args_size(c, P, L) : args_size32(c, P, L)).cache;
@@ -1189,8 +1190,11 @@ void fmg_start(mlsgd_ctx* c, Plan* P) {
              L.Bf + (size_t)gr.p0 * srow(gr.n), s);
     }
   }
-  // kb: the largest grid whose start is ready
-  const bool small = small_cycle<T>(c, P), mid = mid_cycle<T>(c, P);
+  // kb: the largest grid whose start is ready.  Event timing of the smoothing
+  // steps on 9^3 and below keeps the passes of the start there, the only ones of
+  // a solve on these grids (its cycles run them in one kernel, timed or not).
+  const bool timed = c->tm.on && c->tm.kind == 1 && c->tm.n <= 9;
+  const bool small = !timed && small_cycle<T>(c, P), mid = !timed && mid_cycle<T>(c, P);
   const int kb = mid ? S - 4 : small ? S - 3 : S - 1;
   for (int k = 0; k < kb; ++k) {
     SizeLvl& L = P->sizes[k];
@@ -1323,7 +1327,9 @@ void flush_steps(mlsgd_ctx* c, Plan* P) {
 bool cg_small_applies(const mlsgd_ctx* c, const Plan* P) {
   if (c->pb.solver != MLSGD_SOLVER_CG || c->force_restart) return false;
   for (const auto& gr : P->groups)
-    if (gr.n > CG_SMALL_MAX || !P->sizes[gr.sl].C || (c->tm.on && c->tm.n == gr.n)) return false;
+    if (gr.n > CG_SMALL_MAX || !P->sizes[gr.sl].C ||
+        (c->tm.on && c->tm.kind == 4 && c->tm.n == gr.n))
+      return false;
   return true;
 }
 
