@@ -322,8 +322,10 @@ int mlsgd_set_graph(mlsgd_ctx* ctx, int enable);
  * grid is bracketed by HIP events on the context's stream: the plain
  * smoothing step (enable = 1), the fused two-step post-smoothing pass
  * (enable = 2), the fused pre-smoothing pass with its residual (enable = 3)
- * or the Krylov matvec (enable = 4); the fused passes run on grids with
- * 64-wide tiles of height 8 or 16 and a cached coefficient.  Timing keeps, on
+ * or the Krylov matvec (enable = 4).  The fused passes run with a cached
+ * coefficient on grids of 11 and more vertices, except in tiles of height 4.  The
+ * matvec is timed in launches of one grid size, where an untimed call of several
+ * sizes runs one launch over them all.  Timing keeps, on
  * the timed grid, passes that one kernel would otherwise do together, so what
  * it times there is no part of an untimed call and results differ from one's by
  * rounding: the smoothing passes of 17^3 (enable = 1, 2, 3), the plain steps of

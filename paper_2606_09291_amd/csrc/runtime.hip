@@ -728,11 +728,12 @@ double jac_bytes(int n, int rows, bool x_zero, bool prolong, const GridArgs&) {
 
 // Algorithmic bytes of the fused pre-smoothing pass from x = 0: b read, x2
 // written, and the residual (half: its x-restricted half, on every second
-// plane) written (coefficient and reciprocal diagonal: 0 bytes).
+// plane; direct: the coarse right-hand side) written (coefficient and reciprocal
+// diagonal: 0 bytes).
 template <typename T>
-double pre2r_bytes(int n, int rows, bool half) {
+double pre2r_bytes(int n, int rows, bool half, bool direct) {
   const double N = (double)rows * (double)(n - 2) * (double)(n - 2) * (double)(n - 2);
-  return N * (half ? 2.5 : 3.0) * (double)sizeof(T);
+  return N * (direct ? 2.125 : half ? 2.5 : 3.0) * (double)sizeof(T);
 }
 
 // Algorithmic bytes of the Krylov matvec: z read (z_bytes per point), p_old
@@ -907,7 +908,7 @@ void vcycle_cheb(mlsgd_ctx* c, Plan* P, int k0 = 0, int rlim = INT_MAX, bool xin
       const bool half = c->pre2r_half && pre2r_half_tiles(g);
       const bool direct = half && pre2r_to_coarse(g);   // the whole restriction too
       T* const bc = mg_view<T>(P->sizes[k + 1]).B;
-      timed_launch(c, g, pre2r_bytes<T>(L.n, g.rows, half), [&] {
+      timed_launch(c, g, pre2r_bytes<T>(L.n, g.rows, half, direct), [&] {
         march_pre2r<T>(g, dinv, v.B, A[1], direct ? bc : A[0], om[0], om[1], half, c->stream);
       }, 3);
       if (!half)
