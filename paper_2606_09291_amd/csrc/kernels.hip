@@ -143,6 +143,11 @@ __device__ __forceinline__ double block_sum(double v, double* sred) {
 
 static inline int cdiv(long long a, long long b) { return (int)((a + b - 1) / b); }
 
+// Most workgroups of 256 threads in one launch: a launch holds fewer than 2^32
+// threads.  Launches over several grid sizes whose workgroups add up to more are
+// made in parts.
+constexpr long long MAX_WG256 = (1LL << 24) - 1;
+
 // A workgroup marches its chunk at about a memory round trip per plane, so a
 // batch too small to fill the chip takes as long as one chunk.  With the batch's
 // rows known, the chunk is halved (to even lengths) while that shortens the
@@ -3474,6 +3479,17 @@ void field_caches(FieldTable& ft, const double* coef, int K, hipStream_t s) {
       else d64 = true;
     }
   }
+  if (std::max(cb, db) > MAX_WG256 && ft.count > 1) {
+    const int half = ft.count / 2;
+    FieldTable lo{}, hi{};
+    for (int k = 0; k < ft.count; ++k) {
+      FieldTable& h = k < half ? lo : hi;
+      h.lv[h.count++] = ft.lv[k];
+    }
+    field_caches(lo, coef, K, s);
+    field_caches(hi, coef, K, s);
+    return;
+  }
   if (cb > 0)
     hipLaunchKernelGGL(k_coef_cache, dim3((unsigned)cb), dim3(256), 0, s, ft, coef, K);
   if (db <= 0) return;
@@ -4299,17 +4315,19 @@ static void launch_group(const GridArgs& g, double* a, const double* b, double* 
 
 template <int OP>
 static void launch_groups(GroupTable& t, const int* poff, double* partial, hipStream_t s) {
-  if (t.count == 1) {
-    const GroupRows& r = t.gr[0];
-    launch_group<OP>(r.g, r.a, r.b, r.c, r.d, poff, partial, r.cf, s);
+  long long wg = 0;
+  for (int i = 0; i < t.count; ++i) {
+    t.gr[i].begin = (int)wg;
+    wg += (long long)t.gr[i].g.rows * t.gr[i].g.t.tiles_per_row;
+  }
+  if (t.count == 1 || wg > MAX_WG256) {
+    for (int i = 0; i < t.count; ++i) {
+      const GroupRows& r = t.gr[i];
+      launch_group<OP>(r.g, r.a, r.b, r.c, r.d, poff, partial, r.cf, s);
+    }
     return;
   }
-  int wg = 0;
-  for (int i = 0; i < t.count; ++i) {
-    t.gr[i].begin = wg;
-    wg += t.gr[i].g.rows * t.gr[i].g.t.tiles_per_row;
-  }
-  if (wg > 0) hipLaunchKernelGGL((k_groups<OP>), dim3(wg), dim3(256), 0, s, t, poff, partial);
+  if (wg > 0) hipLaunchKernelGGL((k_groups<OP>), dim3((unsigned)wg), dim3(256), 0, s, t, poff, partial);
 }
 
 void group_dot(const GridArgs& g, const double* a, const double* b, const int* poff,
