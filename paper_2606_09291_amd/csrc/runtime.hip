@@ -206,6 +206,7 @@ struct mlsgd_ctx {
   bool post2 = true;        // fused two-step post-smoothing pass where it applies
   bool vsmall = true;       // the cycle from 9^3 down as one kernel where it applies
   bool xdefer = true;       // x's Krylov step applied by the next matvec
+  bool groups = true;       // Krylov passes of all grid sizes in one launch where they apply
   bool fmg = true;          // full-multigrid start of the Krylov solves
   double fmg_margin = 0.7;  // recursive-residual target as a fraction of rtol after that start
   // Krylov iterations whose active count the host does not read (no solve
@@ -1127,12 +1128,26 @@ static_assert(MAX_GROUPS >= MLSGD_MAX_LEVELS, "a group per level");
 // The launch arguments of every group for one launch over them all; false where
 // there is one group or a group's tiles are not in that kernel.
 bool march_table(mlsgd_ctx* c, Plan* P, bool skip_inactive, MarchTable& t) {
-  if (P->groups.size() < 2 || P->groups.size() > MAX_GROUPS) return false;
+  if (!c->groups || P->groups.size() < 2 || P->groups.size() > MAX_GROUPS) return false;
   for (auto& gr : P->groups) {
     t.gr[t.count].g = args_group(c, P, gr, skip_inactive);
     if (!group_tiles(t.gr[t.count++].g)) return false;
   }
   return true;
+}
+
+// An op over the rows of a table, or of each group by itself.
+template <typename F>
+void each_group(const mlsgd_ctx* c, GroupTable& t, F&& op) {
+  if (c->groups) {
+    op(t);
+    return;
+  }
+  for (int i = 0; i < t.count; ++i) {
+    GroupTable one{};
+    one.gr[one.count++] = t.gr[i];
+    op(one);
+  }
 }
 
 // The residual b0 - A x of every group: stored in the B rows of the top grids,
@@ -1308,7 +1323,8 @@ void krylov_step(mlsgd_ctx* c, Plan* P, bool mg, int it) {
                    P->d_poff, P->d_partial, r32, s);
     gr.pcur ^= 1;
   }
-  if (defer) group_rupdate(gt, P->d_poff, P->d_partial, s);
+  if (defer)
+    each_group(c, gt, [&](GroupTable& t) { group_rupdate(t, P->d_poff, P->d_partial, s); });
 }
 
 // Apply every pending step x += alpha p (active problems and those that
@@ -1319,7 +1335,7 @@ void flush_steps(mlsgd_ctx* c, Plan* P) {
   for (auto& gr : P->groups)
     t.gr[t.count++] =
         GroupRows{args_group(c, P, gr, true), gr.x, gr.p[0], nullptr, gr.p[1], nullptr, 0};
-  group_xflush(t, c->stream);
+  each_group(c, t, [&](GroupTable& g) { group_xflush(g, c->stream); });
 }
 
 // Plain CG where every top grid is small enough for one workgroup: whole
@@ -2108,6 +2124,7 @@ int mlsgd_create(mlsgd_ctx** out, const mlsgd_problem* pb, void* stream) {
     if (const char* e = getenv("MLSGD_POST2")) c->post2 = atoi(e) != 0;
     if (const char* e = getenv("MLSGD_VSMALL")) c->vsmall = atoi(e) != 0;
     if (const char* e = getenv("MLSGD_XDEFER")) c->xdefer = atoi(e) != 0;
+    if (const char* e = getenv("MLSGD_GROUPS")) c->groups = atoi(e) != 0;
     if (const char* e = getenv("MLSGD_FMG")) c->fmg = atoi(e) != 0;
     if (const char* e = getenv("MLSGD_FMG_MARGIN")) c->fmg_margin = atof(e);
     if (const char* e = getenv("MLSGD_FORCE_RESTART")) c->force_restart = atoi(e) != 0;
