@@ -2730,12 +2730,15 @@ __global__ void __launch_bounds__(64 * VM_WAVES)
 // M9 / M17) a first round always pays and a second only if 17^3 fills half of the
 // first: 2000 / 2 1.89 / 1.73, 2300 / 2 (258 workgroups) 2.18 / 2.21, 3000 / 32
 // 2.38 / 2.50, 3000 / 128 (476) 2.78 / 2.73, 3600 / 128 (543) 2.92 / 3.14, 1024 / 512
-// (683) 3.18 / 3.23, 16384 / 64 7.98 / 9.82.  FP32 cycles gain up to four rounds:
-// 8000 / 2 (891) 3.49 / 3.45, 6000 / 256 (951) 3.70 / 3.54, 4096 / 512 (1024) 3.85 /
-// 3.69, 10000 / 512 (1681) 5.90 / 6.33, 17^3 alone 1024 3.39 / 3.20, 1536 5.15 / 5.23.
+// (683) 3.18 / 3.23, 16384 / 64 7.98 / 9.82.  FP32 cycles gain up to five rounds:
+// 8000 / 2 (891) 3.49 / 3.45, 4096 / 512 (1024) 3.85 / 3.69, 8000 / 256 (1173) 4.51 /
+// 4.42, 10000 / 128 (1254) 4.76 / 4.68, 10000 / 256 (1396) 5.20 / 5.23, 10000 / 512
+// (1681) 5.90 / 6.33, 17^3 alone 1024 3.39 / 3.20, 1536 5.15 / 5.23.
 bool mid_rows(int rows17, int tops9, int elem) {
   const int packs = cdiv(tops9, VM_WAVES);
-  if (elem == 4 || packs == 0) return rows17 + packs <= 1024;
+  if (rows17 > 1024) return false;
+  if (packs == 0) return true;
+  if (elem == 4) return rows17 + packs <= 1280;
   return rows17 + packs <= 256 || (rows17 >= 128 && rows17 + packs <= 512);
 }
 

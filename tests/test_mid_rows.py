@@ -34,15 +34,15 @@ def test_rule():
     assert not rule(127, 130, 8) and rule(128, 129, 8)
     assert rule(256, 256, 8) and not rule(256, 257, 8) and not rule(512, 1, 8)
     assert not rule(64, 8000, 8) and not rule(2, 1 << 20, 8)
-    assert rule(2, 1022, 4) and not rule(2, 1023, 4)
-    assert rule(1023, 1, 4) and not rule(1024, 1, 4) and rule(1024, 0, 4)
+    assert rule(2, 1278, 4) and not rule(2, 1279, 4)
+    assert rule(1024, 256, 4) and not rule(1024, 257, 4) and not rule(1025, 0, 4)
 
 
 @pytest.mark.gpu
 @pytest.mark.parametrize("precision,M", [
     ("fp64", [2284, 2]), ("fp64", [2285, 2]),          # 256 and 257 workgroups
     ("fp64", [3328, 128]), ("fp64", [3329, 128]),      # 512 and 513
-    ("mixed", [9196, 2]), ("mixed", [9197, 2])])       # 1024 and 1025
+    ("mixed", [11500, 2]), ("mixed", [11501, 2])])     # 1280 and 1281
 def test_estimates_around_the_lines(monkeypatch, precision, M):
     import torch
     if not torch.cuda.is_available():
