@@ -148,7 +148,8 @@ KERNEL_NAMES = {
     3: ("fused pre-smoothing pass (k_pre2v, k_pre2r: two Chebyshev steps from zero, residual restricted "
         "along x, cached 1/a and 1/D) on the {n}^3 rows"),
     4: ("Krylov matvec (k_march OP_MATVEC: p = z + beta p, q = A p, deferred x step, cached 1/a) "
-        "on the {n}^3 rows"),
+        "on the {n}^3 rows, launched by themselves for the timing (an untimed estimate runs the "
+        "grids of all sizes in one launch, k_march_groups)"),
 }
 
 

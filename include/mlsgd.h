@@ -26,6 +26,11 @@
  *   - Inner products: <a, b>_h = h^3 sum over interior vertices.  Gradients
  *     are L^2_h Riesz representers on the finest grid.
  *
+ * Reproducibility: a call repeated with the same arguments gives the same
+ * bits.  A sample's solution depends on the batch it is solved in by rounding
+ * only: the lengths of the kernels' chunks, and with them the order of partial
+ * sums, and the kernels of the grids up to 17^3 follow the number of problems.
+ *
  * Memory: every array argument marked "device" is a device pointer owned by
  * the caller, contiguous, read or written asynchronously on the context's
  * stream.  Host arguments are read before the call returns.  Stats structs
@@ -195,7 +200,8 @@ int mlsgd_solve_state_adjoint(mlsgd_ctx* ctx, int level, int coarse,
  * 86 bytes per vertex of the solved grid in FP64: two 65^3 samples fit, three
  * do not, and no 129^3 sample does), when kernel timing is on, or when the
  * context's device is not current; such a call returns before any work is
- * enqueued. */
+ * enqueued.  Results equal mlsgd_solve_state_adjoint's bit for bit, or, where
+ * the array holds the batch only with fewer partial sums, up to rounding. */
 int mlsgd_solve_state_adjoint_noalloc(mlsgd_ctx* ctx, int level, int coarse,
                                       int64_t first, int64_t count,
                                       const double* u_fine, double* y_out,

@@ -688,9 +688,13 @@ __global__ void __launch_bounds__(TY* TZ)
 // One FP64 op over the rows of several groups (grids of different size, cached
 // coefficient) in one launch: a small group's launch takes the latency of one
 // march on a nearly idle chip, and these run side by side.  Workgroups have the
-// 512 threads of the largest tile and take several smaller tiles at once; waves
-// of a tile that ends early (an inactive problem, a shorter last chunk) leave,
-// and barriers wait for the others only.  A group's workgroups start at a
+// 512 threads of the largest tile and take several smaller tiles at once.  A
+// tile is whole waves with LDS of its own, and only its own waves read what they
+// write; waves of a tile that ends early (an inactive problem, a shorter last
+// chunk) leave, and tiles may stand at different barriers of the code.  That rests
+// on the machine's barrier, not on the language's: s_barrier counts the waves of a
+// workgroup that arrive, at whichever s_barrier, and those that ended, so the waves
+// of one tile pass each of theirs together.  A group's workgroups start at a
 // multiple of 8, which keeps its tiles in XCD order.
 // With the residual update likewise (k_groups): a 17^3..65^3 law estimate 4.92 ->
 // 4.52 ms, graph replay of a 64/16/4 estimate 2.32 -> 1.96, an objective up to
@@ -1488,9 +1492,11 @@ __global__ void __launch_bounds__(TY* TZ)
 // a lane owns V = 2 (FP64) or 4 (FP32) consecutive z points of one row: loads
 // and stores are 16 bytes a lane, half or three quarters of the z neighbours
 // are the lane's own, and a workgroup holds whole z lines, so the rings exist
-// in y alone.  That is about 175 VALU and 15-20 LDS instructions per 128 (FP64)
-// or 256 (FP32) points.  One barrier a plane: the planes in LDS are double
-// buffered.
+// in y alone.  On the 129^3 rows a wave's plane step issues 162 VALU and 12 LDS
+// instructions (pre-smoothing) or 169 and 17 (post-smoothing) per 128 points in
+// FP64, 220 and 13 or 240 and 23 per 256 in FP32; the VALU is busy 0.4-0.5 of
+// the time, and waves wait for memory or LDS half of theirs.  One barrier a plane:
+// the planes in LDS are double buffered.
 //
 // A workgroup forms the middle stage on R rows (thread = row x lane) and the
 // output on the R - 2 inner ones; the first and last row's threads also load
@@ -1539,9 +1545,9 @@ VTile make_vtile(int n, int elem, int tile_y, int xchunk, int rows) {
   // y, 1/a and the middle stage of two planes; the coarse ring or (full tiles)
   // the x-restricted plane
   v.lds = (6 * (v.R + 2) * v.PZ + std::max(4 * v.cyn * v.czn, (v.R + 2) * v.PZ) + V) * elem;
-  // The chunk: as split_chunk, but also longer than the given one, up to the
-  // whole line.  Odd chunk lengths stay as given (the x-restricted residual
-  // needs even ones).
+  // The chunk: the least of split_chunk's cost (without its 15% threshold), over
+  // halves of the given length and also longer ones, up to the whole line.  Odd
+  // chunk lengths stay as given (the x-restricted residual needs even ones).
   int best = m <= xchunk ? m : xchunk;
   if (rows > 0 && (m <= xchunk || xchunk % 2 == 0)) {
     const long long fit = 256LL * max(1, 12 / cdiv(threads, 64));
@@ -4351,8 +4357,8 @@ void group_rupdate(GroupTable& t, const int* poff, double* partial, hipStream_t 
 void group_xflush(GroupTable& t, hipStream_t s) { launch_groups<G_XFLUSH>(t, nullptr, nullptr, s); }
 
 // ---------------------------------------------------------------------------
-// Per-problem scalar steps, one workgroup for all problems (fixed summation
-// order; integer count reduced in LDS).
+// Per-problem scalar steps (fixed summation order; the count of active problems
+// an integer).
 // ---------------------------------------------------------------------------
 // LP lanes per problem sum its partial slots and the first of them takes the
 // step.  The launch picks LP by the longest slot list: one thread alone walked
